@@ -451,7 +451,7 @@ ebmg_status ebmg_kernel_timing(ebmg_problem pb, int32_t which, int32_t level, in
 /* Paper: Radiative transfer (eq. `sp1` and its Robin outflow condition,
  * eq. `robin`), Helmholtz equations (its backward-Euler example).
  * Replace the coefficients of a problem without embedded objects and without
- * explicit rows on any level (e.g. the Eddington Helmholtz problem of the
+ * explicit rows on the finest level (e.g. the Eddington Helmholtz problem of the
  * radiative-transfer section, kappa phi - div((1/3kappa) grad phi) = S, for a
  * new absorption kappa): alpha, beta, a_gas, a_diel, b_gas in opt and the
  * boundary data in bc (values and Robin a1/a2; kinds must equal those given

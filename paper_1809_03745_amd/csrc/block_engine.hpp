@@ -556,8 +556,9 @@ __device__ void be_restrict_cells_part(const BLev<T>& F, const BLev<T>& Cl, cons
   FP_EXACT_ORDER
   constexpr int U = BeU<T>::U;
   const int cnx = Cl.n[0], cny = Cl.n[1];
-  const int fnx = 2 * cnx;
-  const int64_t fsxy = (int64_t)fnx * 2 * cny;
+  const int fnx = F.n[0], fny = F.n[1];
+  const int fsxy = fnx * fny;
+  const int last = F.N - 1;   // cells with missing children (odd extents) are non-simple: loads clamped, unused
   const int CN = Cl.N;
   const T w = DIM == 3 ? T(0.125) : T(0.25);
   const int end = be_end(CN, beg, cnt);
@@ -572,17 +573,17 @@ __device__ void be_restrict_cells_part(const BLev<T>& F, const BLev<T>& Cl, cons
       const int JK = P / cnx;
       const int J = JK % cny;
       const int K = DIM == 3 ? JK / cny : 0;
-      const int64_t c0 = 2 * I + (int64_t)fnx * (2 * J) + (DIM == 3 ? fsxy * (2 * K) : 0);
+      const int c0 = 2 * I + fnx * (2 * J) + (DIM == 3 ? fsxy * (2 * K) : 0);
       tg[u] = Cl.tag[P];
       v[u][0] = rf[c0];
-      v[u][1] = rf[c0 + 1];
-      v[u][2] = rf[c0 + fnx];
-      v[u][3] = rf[c0 + fnx + 1];
+      v[u][1] = rf[min(c0 + 1, last)];
+      v[u][2] = rf[min(c0 + fnx, last)];
+      v[u][3] = rf[min(c0 + fnx + 1, last)];
       if (DIM == 3) {
-        v[u][4] = rf[c0 + fsxy];
-        v[u][5] = rf[c0 + fsxy + 1];
-        v[u][6] = rf[c0 + fsxy + fnx];
-        v[u][7] = rf[c0 + fsxy + fnx + 1];
+        v[u][4] = rf[min(c0 + fsxy, last)];
+        v[u][5] = rf[min(c0 + fsxy + 1, last)];
+        v[u][6] = rf[min(c0 + fsxy + fnx, last)];
+        v[u][7] = rf[min(c0 + fsxy + fnx + 1, last)];
       }
     }
 #pragma unroll
@@ -632,7 +633,7 @@ __device__ void be_prolong_cells_part(const BLev<T>& F, const BLev<T>& Cl, const
   FP_EXACT_ORDER
   constexpr int U = BeU<T>::U;
   const int fnx = F.n[0], fny = F.n[1];
-  const int cnx = fnx >> 1, cny = fny >> 1;
+  const int cnx = (fnx + 1) >> 1, cny = (fny + 1) >> 1;
   const int FN = F.N;
   const int end = be_end(FN, beg, cnt);
   for (int c0 = beg + (int)threadIdx.x; c0 < end; c0 += blockDim.x * U) {

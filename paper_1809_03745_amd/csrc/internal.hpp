@@ -128,6 +128,11 @@ struct Level {
   std::vector<int8_t> primary;
   std::vector<int32_t> sec_of;
   std::vector<int32_t> sec_cell;
+  // part of the last cell of each axis that lies in the box (below 1 under an
+  // odd extent), and the cells that hold fine template cells of one phase only
+  // (empty on the finest level: its template cells)
+  double fill[3] = {1, 1, 1};
+  std::vector<uint8_t> pure;
   // regular template: A phi_i = diag_i phi_i + coff[p] * sum_nb phi_nb,
   // diag_i = d0[p] + sum over touched domain faces f of cb[f][p]
   double coff[2] = {0, 0};
@@ -192,6 +197,7 @@ void fine_template(Problem& pb);
 void coarse_template(Level& C, const Problem& pb);
 void build_bottom(Problem& pb);
 void colour_irregular(Level& L);
+void coarse_rows(const Problem& pb, const Level& L, Level& C);
 void host_rhs(const Problem& pb, const double* rho, const double* sigma, const double* bcv,
               const double* objv, double* b);
 

@@ -1378,13 +1378,14 @@ __global__ void __launch_bounds__(kBlock) k_resid_irr(int nrows, const int64_t* 
 }
 
 // Restriction in one launch: blocks [0, nbc) take simple coarse cells (mean
-// of the 2^D children; covered coarse cells get 0), blocks [nbc, nbc + nbn)
+// of the 2^D children, fine extents fnx and fny; covered coarse cells get 0;
+// coarse cells with fewer children are non-simple), blocks [nbc, nbc + nbn)
 // the non-simple coarse unknowns from their child lists, and the rest clear
 // the coarse correction xc (cells and second-phase unknowns).
 template <typename T, int DIM>
 __global__ void __launch_bounds__(kBlock) k_restrict_all(const uint8_t* __restrict__ ctag, const T* __restrict__ rf,
                                                          T* __restrict__ bc, T* __restrict__ xc, int cnx, int cny,
-                                                         int cnz, unsigned nbc, unsigned nbn, int nns,
+                                                         int cnz, int fnx, int fny, unsigned nbc, unsigned nbn, int nns,
                                                          const int64_t* __restrict__ cdof,
                                                          const int32_t* __restrict__ ptr,
                                                          const int64_t* __restrict__ child, int64_t ncd) {
@@ -1404,8 +1405,7 @@ __global__ void __launch_bounds__(kBlock) k_restrict_all(const uint8_t* __restri
     const int64_t JK = P / cnx;
     const int J = (int)(JK % cny);
     const int K = DIM == 3 ? (int)(JK / cny) : 0;
-    const int fnx = 2 * cnx;
-    const int64_t fsxy = (int64_t)fnx * 2 * cny;
+    const int64_t fsxy = (int64_t)fnx * fny;
     const int64_t c0 = 2 * I + (int64_t)fnx * (2 * J) + (DIM == 3 ? fsxy * (2 * K) : 0);
     T s = rf[c0] + rf[c0 + 1] + rf[c0 + fnx] + rf[c0 + fnx + 1];
     if (DIM == 3) s += rf[c0 + fsxy] + rf[c0 + fsxy + 1] + rf[c0 + fsxy + fnx] + rf[c0 + fsxy + fnx + 1];
@@ -1442,7 +1442,7 @@ __global__ void __launch_bounds__(kBlock) k_prolong_all(const uint8_t* __restric
     const int i = (int)(blockIdx.y * blockDim.x + threadIdx.x);
     if (row >= fny * (DIM == 3 ? fnz : 1) || i >= fnx) return;
     const int j = row % fny, k = DIM == 3 ? row / fny : 0;
-    const int cnx = fnx >> 1, cny = fny >> 1;
+    const int cnx = (fnx + 1) >> 1, cny = (fny + 1) >> 1;
     const int64_t c = i + (int64_t)fnx * row;
     const int64_t P = (i >> 1) + (int64_t)cnx * ((j >> 1) + (int64_t)cny * (k >> 1));
     const uint8_t ft = ftag[c], ct = ctag[P];
@@ -1476,7 +1476,7 @@ __global__ void __launch_bounds__(kBlock) k_prolong_q(const uint8_t* __restrict_
     const int i = 4 * (int)(blockIdx.y * blockDim.x + threadIdx.x);
     if (row >= fny * (DIM == 3 ? fnz : 1) || i >= fnx) return;
     const int j = row % fny, k = DIM == 3 ? row / fny : 0;
-    const int cnx = fnx >> 1, cny = fny >> 1;
+    const int cnx = (fnx + 1) >> 1, cny = (fny + 1) >> 1;
     const int64_t c = i + (int64_t)fnx * row;
     const int64_t P = (i >> 1) + (int64_t)cnx * ((j >> 1) + (int64_t)cny * (k >> 1));
     const uint32_t ft = *(const uint32_t*)(ftag + c);

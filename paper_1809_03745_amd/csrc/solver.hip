@@ -917,6 +917,42 @@ static std::vector<int32_t> row_order(const Level& L) {
   return id;
 }
 
+// A level's explicit rows as the device holds them: group by group (red rows,
+// then black rows), so a colour group is a contiguous row range, each row's
+// entries in column order (neighbouring rows of a slice then gather x at
+// neighbouring addresses for the same entry position).
+struct DevRows {
+  std::vector<int64_t> dof, rp;
+  std::vector<int32_t> col;
+  std::vector<double> val, diag;
+};
+static DevRows device_rows(const Level& L) {
+  const int64_t R = (int64_t)L.irow_dof.size();
+  const std::vector<int32_t> perm = row_order(L);
+  DevRows o;
+  o.dof.resize(R);
+  o.diag.resize(R);
+  o.rp.assign(R + 1, 0);
+  o.col.reserve(L.col.size());
+  o.val.reserve(L.val.size());
+  std::vector<std::pair<int32_t, double>> ent;
+  for (int64_t k = 0; k < R; ++k) {
+    const int32_t r = perm[k];
+    o.dof[k] = L.irow_dof[r];
+    o.diag[k] = L.idiag[r];
+    ent.clear();
+    for (int64_t e = L.rp[r]; e < L.rp[r + 1]; ++e) ent.emplace_back((int32_t)L.col[e], L.val[e]);
+    std::stable_sort(ent.begin(), ent.end(), [](const std::pair<int32_t, double>& a,
+                                                const std::pair<int32_t, double>& b) { return a.first < b.first; });
+    for (const auto& pe : ent) {
+      o.col.push_back(pe.first);
+      o.val.push_back(pe.second);
+    }
+    o.rp[k + 1] = (int64_t)o.col.size();
+  }
+  return o;
+}
+
 // Sliced layout of the (device-ordered) explicit rows: each colour group is
 // cut into slices of kSlice rows; entry j of the slice's rows is stored at
 // sl_ptr[slice] + j * kSlice + (row within the slice), padded to the slice's
@@ -946,6 +982,40 @@ static void build_sliced(const std::vector<int64_t>& rp, const std::vector<int32
     }
   }
   grp[2] = (int)sptr.size() - 1;
+}
+
+static std::vector<int32_t> group_ptr(const Level& L) {
+  const int32_t R = (int32_t)L.irow_dof.size();
+  return L.cls_ptr.size() == 3 ? L.cls_ptr : std::vector<int32_t>{0, R, R};
+}
+
+// New values of a resident level's explicit rows (same rows and columns).
+static void update_row_values(DevLevel& d, const Level& L, hipStream_t s) {
+  const DevRows rows = device_rows(L);
+  std::vector<int64_t> sptr;
+  std::vector<int32_t> scol;
+  std::vector<double> sval;
+  int grp[3];
+  build_sliced(rows.rp, rows.col, rows.val, group_ptr(L), sptr, scol, sval, grp);
+  auto put64 = [&](DevBuf<double>& b, const std::vector<double>& v) {
+    if (!b.p) return;
+    if (b.n != (int64_t)v.size()) throw ArgError("explicit rows changed size");
+    HIPCHECK(hipMemcpyAsync(b.p, v.data(), sizeof(double) * v.size(), hipMemcpyHostToDevice, s));
+    HIPCHECK(hipStreamSynchronize(s));
+  };
+  auto put32 = [&](DevBuf<float>& b, const std::vector<double>& v) {
+    if (!b.p) return;
+    if (b.n != (int64_t)v.size()) throw ArgError("explicit rows changed size");
+    const std::vector<float> f(v.begin(), v.end());
+    HIPCHECK(hipMemcpyAsync(b.p, f.data(), sizeof(float) * f.size(), hipMemcpyHostToDevice, s));
+    HIPCHECK(hipStreamSynchronize(s));
+  };
+  put64(d.val64, rows.val);
+  put64(d.diag64, rows.diag);
+  put64(d.sl_val64, sval);
+  put32(d.val32, rows.val);
+  put32(d.diag32, rows.diag);
+  put32(d.sl_val32, sval);
 }
 
 // Whether two levels (of family members on one geometry) have the same
@@ -986,34 +1056,12 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
       D.shared_bytes += d.tag.share(sd->tag);
     else
       d.tag.upload(L.tag.data(), L.N, s, by);
-    // explicit rows are stored on the device group by group (red rows, then
-    // black rows), so a colour group is a contiguous row range
-    const std::vector<int32_t> perm = row_order(L);
-    std::vector<int64_t> idof(d.R), rp(d.R + 1, 0);
-    std::vector<int32_t> col, ident(d.R);
-    std::vector<double> val, dg(d.R);
-    col.reserve(L.col.size());
-    val.reserve(L.val.size());
-    // each row's entries in column order: neighbouring rows of a slice then
-    // gather x at neighbouring addresses for the same entry position
-    std::vector<std::pair<int32_t, double>> ent;
-    for (int64_t k = 0; k < d.R; ++k) {
-      const int32_t r = perm[k];
-      idof[k] = L.irow_dof[r];
-      dg[k] = L.idiag[r];
-      ent.clear();
-      for (int64_t e = L.rp[r]; e < L.rp[r + 1]; ++e) ent.emplace_back((int32_t)L.col[e], L.val[e]);
-      std::stable_sort(ent.begin(), ent.end(),
-                       [](const std::pair<int32_t, double>& a, const std::pair<int32_t, double>& b) {
-                         return a.first < b.first;
-                       });
-      for (const auto& pe : ent) {
-        col.push_back(pe.first);
-        val.push_back(pe.second);
-      }
-      rp[k + 1] = (int64_t)col.size();
-      ident[k] = (int32_t)k;
-    }
+    const DevRows rows = device_rows(L);
+    const std::vector<int64_t>&idof = rows.dof, &rp = rows.rp;
+    const std::vector<int32_t>& col = rows.col;
+    const std::vector<double>&val = rows.val, &dg = rows.diag;
+    std::vector<int32_t> ident(d.R);
+    for (int64_t k = 0; k < d.R; ++k) ident[k] = (int32_t)k;
     if (sd) {
       D.shared_bytes += d.irow_dof.share(sd->irow_dof) + d.rp.share(sd->rp) + d.col.share(sd->col) +
                         d.cls_rows.share(sd->cls_rows);
@@ -1032,7 +1080,7 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
       d.diag32.upload(g.data(), (int64_t)g.size(), s, by);
     }
     {
-      std::vector<int32_t> gptr = L.cls_ptr.size() == 3 ? L.cls_ptr : std::vector<int32_t>{0, (int32_t)d.R, (int32_t)d.R};
+      const std::vector<int32_t> gptr = group_ptr(L);
       std::vector<int64_t> sptr;
       std::vector<int32_t> scol;
       std::vector<double> sval;
@@ -1393,10 +1441,10 @@ static void restrict_to(DevLevel& f, DevLevel& c, const T* rf, T* bc, T* xc, hip
   const dim3 g(nbc + nbn + nblk(ncd));
   if (f.dim == 3)
     hipLaunchKernelGGL((k_restrict_all<T, 3>), g, dim3(kBlock), 0, s, c.tag.p, rf, bc, xc, c.n[0], c.n[1], c.n[2],
-                       nbc, nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p, ncd);
+                       f.n[0], f.n[1], nbc, nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p, ncd);
   else
-    hipLaunchKernelGGL((k_restrict_all<T, 2>), g, dim3(kBlock), 0, s, c.tag.p, rf, bc, xc, c.n[0], c.n[1], 1, nbc,
-                       nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p, ncd);
+    hipLaunchKernelGGL((k_restrict_all<T, 2>), g, dim3(kBlock), 0, s, c.tag.p, rf, bc, xc, c.n[0], c.n[1], 1, f.n[0],
+                       f.n[1], nbc, nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p, ncd);
   HIPCHECK(hipGetLastError());
 }
 
@@ -1441,7 +1489,7 @@ static void residual_restrict(DevLevel& f, DevLevel& c, const T* x, const T* b, 
   const unsigned nbn = nblk(f.n_ns);
   const int64_t ncd = c.N + c.N2;
   hipLaunchKernelGGL((k_restrict_all<T, 3>), dim3(nbn + nblk(ncd)), dim3(kBlock), 0, s, c.tag.p, r, Vec<T>::b(c),
-                     Vec<T>::x(c), c.n[0], c.n[1], c.n[2], 0u, nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p,
+                     Vec<T>::x(c), c.n[0], c.n[1], c.n[2], f.n[0], f.n[1], 0u, nbn, (int)f.n_ns, f.ns_cdof.p, f.ns_ptr.p, f.ns_child.p,
                      ncd);
   HIPCHECK(hipGetLastError());
 }
@@ -3852,8 +3900,9 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
     drain(pb);
     Problem& H = *pb->host;
     if (!H.geo.obj_value.empty() || H.geo.N2 > 0) throw ArgError("problem has embedded objects");
-    for (const Level& L : H.levels)
-      if (!L.irow_dof.empty()) throw ArgError("problem has explicit rows");
+    // the finest level alone decides: a box of odd extents at some coarser
+    // level carries explicit rows there, whose values are formed again below
+    if (!H.levels[0].irow_dof.empty()) throw ArgError("problem has explicit rows");
     Options o2;
     if (parse_options(opt, 0, o2) != EBMG_OK) throw ArgError("bad options");
     const Options& o = H.opt;
@@ -3879,7 +3928,10 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
     H.aph[0] = o2.a_gas;
     H.aph[1] = o2.a_diel;
     fine_template(H);
-    for (size_t l = 1; l < H.levels.size(); ++l) coarse_template(H.levels[l], H);
+    for (size_t l = 1; l < H.levels.size(); ++l) {
+      coarse_template(H.levels[l], H);
+      if (!H.levels[l].irow_dof.empty()) coarse_rows(H, H.levels[l - 1], H.levels[l]);
+    }
     build_bottom(H);
     if (!pb->on_device) return EBMG_OK;
     HIPCHECK(hipSetDevice(pb->ctx->device));
@@ -3892,6 +3944,7 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
     for (size_t l = 0; l < H.levels.size(); ++l) {
       D.lv[l].t64 = make_tmpl<double>(H.levels[l]);
       D.lv[l].t32 = make_tmpl<float>(H.levels[l]);
+      if (!H.levels[l].irow_dof.empty()) update_row_values(D.lv[l], H.levels[l], s);
     }
     if (!H.bottom_inv.empty()) {
       if ((int64_t)H.bottom_inv.size() != D.bottom.n) throw ArgError("bottom size changed");
