@@ -222,10 +222,23 @@ constexpr int kMeshLeaf = 4;
 // 01, 12, 20 (9), pseudonormals of vertices 0, 1, 2 (9)
 constexpr int kMeshTriDoubles = 30;
 
+// The search reads, per triangle, vertex a, edges ab and ac, ab.ab, ab.ac and
+// ac.ac (kMeshSearchDoubles) and the unit normal, centre and radius of the
+// smallest disc around it (kMeshDiscDoubles, one unused); per tree node an
+// oriented box: |ax[i] . p - c[i]| <= h[i]. Siblings are neighbours, the
+// record of an internal node names its first child as -count.
+constexpr int kMeshSearchDoubles = 12, kMeshDiscDoubles = 8;
+struct MeshBox {
+  double ax[3][3], c[3], h[3];
+  int32_t first, count;
+};
+
 struct MeshHost {
   int32_t ntri = 0;
   int depth = 0;
   std::vector<double> tri;         // kMeshTriDoubles per triangle, in leaf order
+  std::vector<double> search, disc;
+  std::vector<MeshBox> boxes;      // box 0 is the root, box 1 unused
   std::vector<MeshNode> nodes;     // node 0 is the root
 };
 

@@ -102,6 +102,121 @@ struct Builder {
 
 }  // namespace
 
+// Triangle records of the search, in leaf order.
+static void search_data(MeshHost& out, int32_t nt) {
+  out.search.resize((size_t)nt * kMeshSearchDoubles);
+  out.disc.assign((size_t)nt * kMeshDiscDoubles, 0.0);
+  for (int32_t k = 0; k < nt; ++k) {
+    const double* r = &out.tri[(size_t)k * kMeshTriDoubles];
+    const V3 v[3] = {{r[0], r[1], r[2]}, {r[3], r[4], r[5]}, {r[6], r[7], r[8]}};
+    const V3 ab = sub(v[1], v[0]), ac = sub(v[2], v[0]);
+    const double s[kMeshSearchDoubles] = {v[0].x, v[0].y, v[0].z, ab.x, ab.y, ab.z, ac.x, ac.y, ac.z,
+                                          dot(ab, ab), dot(ab, ac), dot(ac, ac)};
+    std::memcpy(&out.search[(size_t)k * kMeshSearchDoubles], s, sizeof(s));
+    // the disc over the longest edge, or the circumscribed one of an acute triangle
+    int e = 0;
+    double len = -1;
+    for (int j = 0; j < 3; ++j)
+      if (norm(sub(v[(j + 1) % 3], v[j])) > len) {
+        len = norm(sub(v[(j + 1) % 3], v[j]));
+        e = j;
+      }
+    V3 c = scl(add(v[e], v[(e + 1) % 3]), 0.5);
+    if (norm(sub(v[(e + 2) % 3], c)) > 0.5 * len) {
+      const V3 n = cross(ab, ac);
+      const V3 o = scl(add(scl(cross(n, ab), dot(ac, ac)), scl(cross(ac, n), dot(ab, ab))), 0.5 / dot(n, n));
+      c = add(v[0], o);
+    }
+    double rad = 0;
+    for (int j = 0; j < 3; ++j) rad = std::max(rad, norm(sub(v[j], c)));
+    const double d[kMeshDiscDoubles] = {r[9], r[10], r[11], c.x, c.y, c.z, rad * (1.0 + 1e-12), 0.0};
+    std::memcpy(&out.disc[(size_t)k * kMeshDiscDoubles], d, sizeof(d));
+  }
+}
+
+// Boxes of the search: axis-aligned on large nodes, on nodes of at most
+// kObbTris triangles along their mean normal where that box has the smaller
+// surface (a patch of a curved surface is thin along its normal: a third of
+// the leaves and triangles examined on a thin cylinder).
+constexpr int32_t kObbTris = 64;
+static void search_boxes(MeshHost& out) {
+  struct Item {
+    int32_t node, box;
+  };
+  out.boxes.assign(2, MeshBox{});
+  out.boxes.reserve(out.nodes.size() + 1);
+  std::vector<Item> st{{0, 0}};
+  // a node's triangles are consecutive: its range by descending to both ends
+  auto range = [&](int32_t n, int32_t& b, int32_t& e) {
+    int32_t a = n;
+    while (out.nodes[a].count < 0) a = out.nodes[a].first;
+    b = out.nodes[a].first;
+    for (a = n; out.nodes[a].count < 0;) a = -out.nodes[a].count;
+    e = out.nodes[a].first + out.nodes[a].count;
+  };
+  while (!st.empty()) {
+    const Item it = st.back();
+    st.pop_back();
+    const MeshNode& n = out.nodes[it.node];
+    MeshBox x{};
+    double size = 0;
+    for (int d = 0; d < 3; ++d) {
+      x.ax[d][d] = 1.0;
+      x.c[d] = 0.5 * (n.lo[d] + n.hi[d]);
+      x.h[d] = 0.5 * (n.hi[d] - n.lo[d]);
+      size = std::max(size, std::max(std::fabs(n.lo[d]), std::fabs(n.hi[d])));
+    }
+    int32_t b, e;
+    range(it.node, b, e);
+    if (e - b <= kObbTris) {
+      V3 m{0, 0, 0};
+      for (int32_t t = b; t < e; ++t) {
+        const double* r = &out.tri[(size_t)t * kMeshTriDoubles];
+        m = add(m, V3{r[9], r[10], r[11]});
+      }
+      if (norm(m) > 1e-9) {
+        m = unit(m);
+        const double a[3] = {std::fabs(m.x), std::fabs(m.y), std::fabs(m.z)};
+        const int k = a[0] < a[1] ? (a[0] < a[2] ? 0 : 2) : (a[1] < a[2] ? 1 : 2);
+        V3 u{k == 0 ? 1.0 : 0.0, k == 1 ? 1.0 : 0.0, k == 2 ? 1.0 : 0.0};
+        u = unit(sub(u, scl(m, dot(u, m))));
+        const V3 f[3] = {m, u, cross(m, u)};
+        MeshBox o{};
+        for (int d = 0; d < 3; ++d) {
+          double lo = 1e300, hi = -1e300;
+          for (int32_t t = b; t < e; ++t) {
+            const double* r = &out.tri[(size_t)t * kMeshTriDoubles];
+            for (int j = 0; j < 3; ++j) {
+              const double q = f[d].x * r[3 * j] + f[d].y * r[3 * j + 1] + f[d].z * r[3 * j + 2];
+              lo = std::min(lo, q);
+              hi = std::max(hi, q);
+            }
+          }
+          o.ax[d][0] = f[d].x;
+          o.ax[d][1] = f[d].y;
+          o.ax[d][2] = f[d].z;
+          o.c[d] = 0.5 * (lo + hi);
+          o.h[d] = 0.5 * (hi - lo);
+        }
+        auto surface = [](const MeshBox& q) { return q.h[0] * q.h[1] + q.h[1] * q.h[2] + q.h[0] * q.h[2]; };
+        if (surface(o) < surface(x)) x = o;
+      }
+    }
+    for (int d = 0; d < 3; ++d) x.h[d] += 1e-14 * size;   // the rounding of the projections
+    if (n.count >= 0) {
+      x.first = n.first;
+      x.count = n.count;
+    } else {
+      const int32_t c = (int32_t)out.boxes.size();
+      x.count = -c;
+      out.boxes.resize(c + 2);
+      st.push_back({n.first, c});
+      st.push_back({-n.count, c + 1});
+    }
+    out.boxes[it.box] = x;
+  }
+}
+
 void build_mesh(const MeshInput& m, MeshHost& out) {
   const int32_t nv = m.nvert, nt = m.ntri;
   if (nv < 4 || nt < 4) throw ArgError("a closed surface needs at least 4 vertices and 4 triangles");
@@ -195,7 +310,9 @@ void build_mesh(const MeshInput& m, MeshHost& out) {
     std::memcpy(&sorted[(size_t)k * kMeshTriDoubles], &out.tri[(size_t)B.order[k] * kMeshTriDoubles],
                 sizeof(double) * kMeshTriDoubles);
   out.tri.swap(sorted);
+  search_data(out, nt);
   out.nodes.swap(B.nodes);
+  search_boxes(out);
   int depth = 0;
   // depth of the tree (for the device traversal stack)
   std::vector<std::pair<int32_t, int>> st{{0, 1}};

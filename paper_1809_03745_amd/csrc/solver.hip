@@ -312,8 +312,8 @@ struct ebmg_problem_s {
 // A triangle mesh resident on the device for signed-distance queries.
 struct ebmg_mesh_s {
   ebmg_ctx ctx = nullptr;
-  ebmg::DevBuf<double> tri;
-  ebmg::DevBuf<uint8_t> nodes;
+  ebmg::DevBuf<double> tri, search, disc;
+  ebmg::DevBuf<uint8_t> boxes;
   ebmg::DevBuf<unsigned long long> visits;   // search counter of the last query
   int32_t ntri = 0, nnode = 0, depth = 0;
   int64_t bytes = 0;
@@ -4635,11 +4635,15 @@ ebmg_status ebmg_mesh_create(ebmg_ctx ctx, int32_t nvert, const double* verts, i
     MeshHost H;
     build_mesh(in, H);
     if (H.depth >= kSdfStack) throw ArgError("mesh tree deeper than the search stack");
-    static_assert(sizeof(MeshNode) == sizeof(DevMeshNode), "node layouts differ");
+    static_assert(sizeof(MeshBox) == sizeof(DevMeshBox), "box layouts differ");
+    static_assert(sizeof(DevSearchTri) == kMeshSearchDoubles * sizeof(double), "search layouts differ");
+    static_assert(sizeof(DevDisc) == kMeshDiscDoubles * sizeof(double), "search layouts differ");
     HIPCHECK(hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
     M->tri.upload(H.tri.data(), (int64_t)H.tri.size(), s, M->bytes);
-    M->nodes.upload((const uint8_t*)H.nodes.data(), (int64_t)(H.nodes.size() * sizeof(MeshNode)), s, M->bytes);
+    M->search.upload(H.search.data(), (int64_t)H.search.size(), s, M->bytes);
+    M->disc.upload(H.disc.data(), (int64_t)H.disc.size(), s, M->bytes);
+    M->boxes.upload((const uint8_t*)H.boxes.data(), (int64_t)(H.boxes.size() * sizeof(MeshBox)), s, M->bytes);
     M->visits.alloc(1, M->bytes);
     HIPCHECK(hipStreamSynchronize(s));
     M->ntri = H.ntri;
@@ -4649,7 +4653,9 @@ ebmg_status ebmg_mesh_create(ebmg_ctx ctx, int32_t nvert, const double* verts, i
   });
   if (st != EBMG_OK) {
     M->tri.release();
-    M->nodes.release();
+    M->search.release();
+    M->disc.release();
+    M->boxes.release();
     M->visits.release();
     return st;
   }
@@ -4676,14 +4682,25 @@ ebmg_status ebmg_mesh_sdf(ebmg_mesh m, const ebmg_box* box, double* sdf, int64_t
       if (box->n[d] < 1) throw ArgError("bad box size");
     if (!(box->h > 0) || !std::isfinite(box->h)) throw ArgError("bad cell size");
     const int m0 = box->n[0] + 1, m1 = box->n[1] + 1, m2 = box->n[2] + 1;
-    const int64_t total = (int64_t)m0 * m1 * m2;
     HIPCHECK(hipSetDevice(ctx->device));
     hipStream_t s = ctx->stream;
     unsigned long long* vis = visits ? m->visits.p : nullptr;
     if (vis) HIPCHECK(hipMemsetAsync(vis, 0, sizeof(unsigned long long), s));
-    const unsigned nb = (unsigned)((total + kSdfBlock - 1) / kSdfBlock);
-    hipLaunchKernelGGL(k_sdf_mesh, dim3(nb), dim3(kSdfBlock), 0, s, (const DevMeshNode*)m->nodes.p, m->tri.p, m0, m1, m2,
-                       box->h, box->lo[0], box->lo[1], box->lo[2], sdf, vis);
+    // 4 x 4 x 4 nodes a wavefront share the most; with fewer than some two
+    // wavefronts a SIMD the walk of the slowest one is the time, and smaller
+    // bricks shorten it (pin, 33^3 nodes: 0.63 against 0.41 ms; 65^3: 0.52
+    // against 0.55)
+    auto launch = [&](auto kernel, int bx, int by, int bz) {
+      const int64_t nw = (int64_t)((m0 + bx - 1) / bx) * ((m1 + by - 1) / by) * ((m2 + bz - 1) / bz);
+      const int64_t nb = (nw + kSdfBlock / 64 - 1) / (kSdfBlock / 64);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kSdfBlock), 0, s, (const DevMeshBox*)m->boxes.p,
+                         (const DevDisc*)m->disc.p, (const DevSearchTri*)m->search.p, m->tri.p, m0, m1, m2, box->h,
+                         box->lo[0], box->lo[1], box->lo[2], sdf, vis);
+    };
+    if ((int64_t)m0 * m1 * m2 >= 64 * 2048)
+      launch(k_sdf_mesh<4, 4, 4>, 4, 4, 4);
+    else
+      launch(k_sdf_mesh<4, 2, 2>, 4, 2, 2);
     HIPCHECK(hipGetLastError());
     if (visits) {
       unsigned long long v = 0;
@@ -4702,7 +4719,9 @@ ebmg_status ebmg_mesh_release(ebmg_mesh m) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
   m->tri.release();
-  m->nodes.release();
+  m->search.release();
+  m->disc.release();
+  m->boxes.release();
   m->visits.release();
   delete m;
   ctx_unref(ctx);
