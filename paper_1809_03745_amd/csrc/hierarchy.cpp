@@ -401,14 +401,15 @@ void build_hierarchy(Problem& pb) {
   build_bottom(pb);
 }
 
-// Dense FP64 inverse of the coarsest level (left empty above 4096 unknowns,
-// where the bottom is relaxed instead).
+// Dense FP64 inverse of the coarsest level (left empty above kBottomMax
+// unknowns, where the bottom is solved by Krylov iterations, and where the
+// device forms it).
 void build_bottom(Problem& pb) {
   const Level& B = pb.levels.back();
   const int64_t n = B.ndof();
   pb.bottom_n = n;
   pb.bottom_inv.clear();
-  if (n > 4096) return;  // bottom solved by relaxation sweeps instead
+  if (n > kBottomMax || !pb.host_bottom) return;
   std::vector<double> A(n * n, 0.0);
   std::vector<std::pair<int64_t, double>> rowbuf;
   for (int64_t q = 0; q < n; ++q) {

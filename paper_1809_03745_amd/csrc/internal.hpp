@@ -188,6 +188,7 @@ struct Problem {
   std::vector<Level> levels;
   FineData fine;
   std::vector<double> bottom_inv;  // dense inverse of the coarsest level
+  bool host_bottom = true;         // false: formed on the device instead
   int64_t bottom_n = 0;
 };
 
@@ -195,6 +196,7 @@ void build_fine_level(Problem& pb);
 void build_hierarchy(Problem& pb);
 void fine_template(Problem& pb);
 void coarse_template(Level& C, const Problem& pb);
+constexpr int64_t kBottomMax = 4096;   // unknowns up to which the bottom level has a dense inverse
 void build_bottom(Problem& pb);
 void colour_irregular(Level& L);
 void coarse_rows(const Problem& pb, const Level& L, Level& C);

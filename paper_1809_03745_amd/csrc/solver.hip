@@ -27,6 +27,7 @@
 
 #include "internal.hpp"
 #include "block_engine.hpp"
+#include "dense_inverse.hpp"
 #include "batch_wide.hpp"
 #include "kernels.hpp"
 #include "zq_kernels.hpp"
@@ -185,6 +186,10 @@ struct DevProblem {
   std::vector<DevLevel> lv;
   DevBuf<double> bottom;
   int64_t bottom_n = 0;
+  // work of the bottom inverse: two matrices; row places, row order twice, flag
+  // (kept where new coefficients may come)
+  DevBuf<double> inv_w;
+  DevBuf<int32_t> inv_i;
   // rhs data of irregular rows
   DevBuf<int64_t> icell;
   DevBuf<double> isrc, iface, icobj, icsig;
@@ -245,7 +250,7 @@ struct DevProblem {
     kt[1].reset();
     for (auto& l : lv) l.release();
     lv.clear();
-    bottom.release(); icell.release(); isrc.release(); iface.release(); icobj.release(); icsig.release();
+    bottom.release(); inv_w.release(); inv_i.release(); icell.release(); isrc.release(); iface.release(); icobj.release(); icsig.release();
     iobj.release(); ecell.release(); erp.release(); ecol.release(); eobj.release(); eval.release();
     eface.release(); ecobj.release(); ecsig.release(); objv.release(); part.release(); scal.release();
     for (auto& k : kv) k.release();
@@ -721,9 +726,11 @@ static void upload_tail(DevProblem& D, hipStream_t s) {
   D.tail_l0 = -1;
   std::vector<BLev<T>> v;
   for (int l = 0; l < nl; ++l) v.push_back(make_blev<T>(D.lv[l]));
-  int64_t by = 0;
-  D.tail_lv.upload((const uint8_t*)v.data(), (int64_t)(v.size() * sizeof(BLev<T>)), s, by);
-  D.bytes += by;
+  const int64_t nb = (int64_t)(v.size() * sizeof(BLev<T>));
+  if (D.tail_lv.n == nb)   // new coefficients: the views in place
+    HIPCHECK(hipMemcpyAsync(D.tail_lv.p, v.data(), nb, hipMemcpyHostToDevice, s));
+  else
+    D.tail_lv.upload((const uint8_t*)v.data(), nb, s, D.bytes);
   HIPCHECK(hipStreamSynchronize(s));
 }
 
@@ -892,6 +899,55 @@ static void upload_bottom_krylov(DevProblem& D, hipStream_t s) {
   HIPCHECK(hipStreamSynchronize(s));
 }
 
+// The dense inverse of the bottom level into D.bottom, from the level's
+// resident rows. Waits for it.
+static void device_bottom(DevProblem& D, bool keep_work, hipStream_t s) {
+  DevLevel& B = D.lv.back();
+  const int n = (int)D.bottom_n;
+  if (!D.bottom.p) D.bottom.alloc((int64_t)n * n, D.bytes);
+  if (!D.inv_w.p) D.inv_w.alloc(2 * (int64_t)n * n, D.bytes);
+  if (!D.inv_i.p) D.inv_i.alloc(3 * (int64_t)n + 1, D.bytes);
+  double *X = D.inv_w.p, *Y = X + (int64_t)n * n;
+  int32_t *src = D.inv_i.p, *perm = src + n, *perm2 = perm + n, *flag = perm2 + n;
+  const int32_t zero = 0;
+  HIPCHECK(hipMemcpyAsync(flag, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
+  const BLev<double> L = make_blev<double>(B);
+  const dim3 gr((unsigned)(B.N + B.R));
+  if (B.dim == 3)
+    hipLaunchKernelGGL((k_dense_rows<3>), gr, dim3(256), 0, s, L, X);
+  else
+    hipLaunchKernelGGL((k_dense_rows<2>), gr, dim3(256), 0, s, L, X);
+  // panel width by the rows a thread of the panel's workgroup holds
+  const int nb = n <= kInvThreads ? 32 : n <= 2 * kInvThreads ? 16 : 8;
+  const unsigned gt = (unsigned)((n + kInvTile - 1) / kInvTile);
+  const int32_t* pin = nullptr;
+  for (int k0 = 0; k0 < n; k0 += nb) {
+#define INV_PANEL(NB, U)                                                                                          hipLaunchKernelGGL((k_inv_panel<NB, U>), dim3(1), dim3(kInvThreads), 0, s, X, Y, n, k0, src, pin, perm, flag);   hipLaunchKernelGGL((k_inv_update<NB>), dim3(gt, gt), dim3(256), 0, s, X, Y, n, k0, src)
+    if (nb == 32) {
+      INV_PANEL(32, 1);
+    } else if (nb == 16) {
+      INV_PANEL(16, 2);
+    } else {
+      INV_PANEL(8, 4);
+    }
+#undef INV_PANEL
+    pin = perm;
+    std::swap(perm, perm2);
+    std::swap(X, Y);
+  }
+  hipLaunchKernelGGL(k_inv_columns, dim3(nblk((int64_t)n * n)), dim3(256), 0, s, X, D.bottom.p, n, pin);
+  HIPCHECK(hipGetLastError());
+  int32_t bad = 0;
+  HIPCHECK(hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipStreamSynchronize(s));
+  if (!keep_work) {
+    D.bytes -= D.inv_w.n * (int64_t)sizeof(double) + D.inv_i.n * (int64_t)sizeof(int32_t);
+    D.inv_w.release();
+    D.inv_i.release();
+  }
+  if (bad) throw GeomError("singular bottom-level operator");
+}
+
 // Device order of a level's explicit rows: by colour group, and within
 // windows of kSortWindow rows of a group by decreasing number of stored
 // entries (host order among equals), so the 64-row slices of the sliced
@@ -1029,6 +1085,13 @@ static bool same_structure(const Level& a, const Level& b) {
          a.np_cdof == b.np_cdof;
 }
 
+// Whether ebmg_set_coefficients applies: no embedded objects, no explicit rows
+// on the finest level (a box of odd extents at some coarser level carries
+// explicit rows there, whose values are formed again).
+static bool recoefficientable(const Problem& H) {
+  return H.geo.obj_value.empty() && H.geo.N2 == 0 && H.levels[0].irow_dof.empty();
+}
+
 // Upload a problem's hierarchy. With `share` (a family member set up on the
 // same geometry as `share`), every level whose structure equals share's
 // takes share's device structure arrays instead of its own copies (the
@@ -1154,8 +1217,10 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
     }
   }
   D.bottom_n = H.bottom_n;
-  D.bottom.upload(H.bottom_inv.data(), (int64_t)H.bottom_inv.size(), s, by);
-  if (D.bottom.n == 0) upload_bottom_krylov(D, s);
+  if (D.bottom_n <= kBottomMax)
+    device_bottom(D, !batch_box && recoefficientable(H), s);
+  else
+    upload_bottom_krylov(D, s);
   // rhs data
   const FineData& F = H.fine;
   const Level& L0 = H.levels[0];
@@ -3041,6 +3106,7 @@ ebmg_status ebmg_setup(ebmg_ctx ctx, const ebmg_box* box, int32_t nobj, const eb
     P->host = std::make_unique<Problem>();
     Problem& H = *P->host;
     if (parse_options(opt, nobj, H.opt) != EBMG_OK) throw ArgError("bad options");
+    H.host_bottom = ctx->device < 0;
     build_host_problem(H, box, nobj, objs, bc);
     if (ctx->device >= 0) {
       HIPCHECK(hipSetDevice(ctx->device));
@@ -3666,6 +3732,7 @@ ebmg_status ebmg_setup_batch(ebmg_ctx ctx, int32_t nbox, const ebmg_box* boxes, 
     auto work = [&]() {
       for (int i = next++; i < nbox; i = next++) {
         try {
+          Bt->boxes[i]->host->host_bottom = false;
           build_host_problem(*Bt->boxes[i]->host, &boxes[i], nobj[i], objs[i], &bcs[i]);
         } catch (const ArgError& e) {
           errs[i] = e.what();
@@ -3899,10 +3966,7 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
   return guard(pb->ctx, [&]() -> ebmg_status {
     drain(pb);
     Problem& H = *pb->host;
-    if (!H.geo.obj_value.empty() || H.geo.N2 > 0) throw ArgError("problem has embedded objects");
-    // the finest level alone decides: a box of odd extents at some coarser
-    // level carries explicit rows there, whose values are formed again below
-    if (!H.levels[0].irow_dof.empty()) throw ArgError("problem has explicit rows");
+    if (!recoefficientable(H)) throw ArgError("problem has embedded objects or explicit rows");
     Options o2;
     if (parse_options(opt, 0, o2) != EBMG_OK) throw ArgError("bad options");
     const Options& o = H.opt;
@@ -3917,7 +3981,7 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
       if (bc->kind[f] == EBMG_BC_ROBIN && !(bc->robin_a2[f] != 0.0)) throw ArgError("Robin a2 must be nonzero");
     }
     if (!(o2.b_gas > 0)) throw ArgError("b must be positive");
-    // host: new template constants on every level and a new bottom inverse
+    // host: new template constants on every level
     H.opt.alpha = o2.alpha;
     H.opt.beta = o2.beta;
     H.opt.a_gas = o2.a_gas;
@@ -3946,17 +4010,12 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
       D.lv[l].t32 = make_tmpl<float>(H.levels[l]);
       if (!H.levels[l].irow_dof.empty()) update_row_values(D.lv[l], H.levels[l], s);
     }
-    if (!H.bottom_inv.empty()) {
-      if ((int64_t)H.bottom_inv.size() != D.bottom.n) throw ArgError("bottom size changed");
-      HIPCHECK(hipMemcpyAsync(D.bottom.p, H.bottom_inv.data(), sizeof(double) * H.bottom_inv.size(),
-                              hipMemcpyHostToDevice, s));
-    } else {
+    if (D.bottom.p)
+      device_bottom(D, true, s);
+    else
       upload_bottom_krylov(D, s);   // its view holds the bottom level's template constants
-    }
     // the one-workgroup engine keeps copies of the templates in its level views
     const int keep = D.tail_l0;
-    D.bytes -= D.tail_lv.n;
-    D.tail_lv.release();
     if (H.opt.precision == EBMG_MIXED)
       upload_tail<float>(D, s);
     else
@@ -4042,6 +4101,7 @@ ebmg_status ebmg_setup_family(ebmg_ctx ctx, const ebmg_box* box, int32_t nobj, c
       P->host = std::make_unique<Problem>();
       Problem& H = *P->host;
       if (parse_options(&opts[k], nobj, H.opt) != EBMG_OK) throw ArgError("bad options");
+      H.host_bottom = ctx->device < 0;
       if (k == 0)
         build_host_problem(H, box, nobj, objs, &bcs[0]);
       else
@@ -4397,6 +4457,7 @@ ebmg_status ebmg_setup_amr(ebmg_ctx ctx, int32_t nbox, const ebmg_box* boxes, co
           lb.kind[f] = EBMG_BC_DIRICHLET;
           lb.value[f] = 0.0;
         }
+      H.host_bottom = ctx->device < 0;
       build_host_problem(H, &boxes[l], nobj[l], objs[l], &lb);
       A->lev.push_back(P.release());
     }
