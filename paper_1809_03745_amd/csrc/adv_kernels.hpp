@@ -1,7 +1,7 @@
 // One explicit advection step of a density on the gas phase of a cut-cell
 // grid (Convection-Diffusion-Reaction equations: Advective discretization,
 // Hybrid divergence), FP64:
-//   k_adv_zm       (3D) the two launches below fused into one z-marching
+//   k_adv_rows     (3D) the two launches below fused into one z-marching
 //                  pass over the box;
 //   k_adv_flux     face-centred fluxes u n_f of one direction, n_f the
 //                  upwind state of an unsplit Godunov predictor with
@@ -31,6 +31,8 @@
 
 namespace ebmg {
 
+constexpr int kAdvX = 60;   // cells of a row a wavefront of k_adv_rows completes
+
 struct AdvGrid {
   int n[3];
   int dim;
@@ -39,11 +41,12 @@ struct AdvGrid {
   double inflow[6];
 };
 
+// sign of the differences times min(2 |dl|, 2 |dr|, |dl + dr| / 2), 0 unless
+// they have the same sign
 __device__ __forceinline__ double adv_mc(double dl, double dr) {
-  if (!(dl * dr > 0.0)) return 0.0;
-  const double dc = 0.5 * (dl + dr);
-  const double m = fmin(fmin(2.0 * fabs(dl), 2.0 * fabs(dr)), fabs(dc));
-  return dc > 0.0 ? m : -m;
+  const double m = fmin(fabs(dl), fabs(dr)), s = dl + dr;
+  const double v = __builtin_copysign(fmin(2.0 * m, fabs(0.5 * s)), s);
+  return dl * dr > 0.0 ? v : 0.0;
 }
 
 template <int DIM>
@@ -153,15 +156,26 @@ __global__ void __launch_bounds__(256) k_adv_full(const uint8_t* __restrict__ cl
   nout[c] = n[c] - G.dt * dc;
 }
 
+// The two cut-cell launches give each cut cell kSub lanes over its list (the
+// lists of neighbouring cells follow each other, so a wavefront's loads are
+// contiguous; one thread per cell took 21 and 29 us for the 69,000 cut cells
+// of a 256^3 pin-plane box).
+__device__ __forceinline__ double adv_list_sum(int64_t b, int64_t e, const double* __restrict__ coef,
+                                               const int64_t* __restrict__ idx, const double* __restrict__ v) {
+  double s = 0.0;
+  for (int64_t q = b + threadIdx.x % kSub; q < e; q += kSub) s += coef[q] * v[idx[q]];
+  for (int off = kSub / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kSub);
+  return s;
+}
+
 __global__ void __launch_bounds__(256) k_adv_dc_cut(int ncut, const int64_t* __restrict__ cell,
                                                     const int64_t* __restrict__ ptr, const int64_t* __restrict__ face,
                                                     const double* __restrict__ coef, const double* __restrict__ F,
                                                     double* __restrict__ Dc) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  const int q = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kSub);
   if (q >= ncut) return;
-  double s = 0.0;
-  for (int64_t e = ptr[q]; e < ptr[q + 1]; ++e) s += coef[e] * F[face[e]];
-  Dc[cell[q]] = s;
+  const double s = adv_list_sum(ptr[q], ptr[q + 1], coef, face, F);
+  if (threadIdx.x % kSub == 0) Dc[cell[q]] = s;
 }
 
 __global__ void __launch_bounds__(256) k_adv_cut(int ncut, const int64_t* __restrict__ cell,
@@ -169,20 +183,15 @@ __global__ void __launch_bounds__(256) k_adv_cut(int ncut, const int64_t* __rest
                                                  const int64_t* __restrict__ nbc, const double* __restrict__ nbw,
                                                  const double* __restrict__ S, const double* __restrict__ Dc,
                                                  double* __restrict__ Dcut, double* __restrict__ give) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  const int q = (int)((blockIdx.x * blockDim.x + threadIdx.x) / kSub);
   if (q >= ncut) return;
   const int64_t c = cell[q];
-  const double dc = Dc[c];
-  if (!(S[q] > 0.0)) {   // no gas neighbour: the conservative divergence stays
-    Dcut[q] = dc;
-    give[q] = 0.0;
-    return;
-  }
-  double dnc = 0.0;
-  for (int64_t e = ptr[q]; e < ptr[q + 1]; ++e) dnc += nbw[e] * Dc[nbc[e]];
-  const double k = kappa[c];
-  Dcut[q] = k * dc + (1.0 - k) * dnc;
-  give[q] = k * (1.0 - k) * (dnc - dc) / S[q];
+  const double dc = Dc[c], sq = S[q], k = kappa[c];
+  const double dnc = adv_list_sum(ptr[q], ptr[q + 1], nbw, nbc, Dc);
+  if (threadIdx.x % kSub != 0) return;
+  // without a gas neighbour the conservative divergence stays
+  Dcut[q] = sq > 0.0 ? k * dc + (1.0 - k) * dnc : dc;
+  give[q] = sq > 0.0 ? k * (1.0 - k) * (dnc - dc) / sq : 0.0;
 }
 
 __global__ void __launch_bounds__(256) k_adv_special(int nsp, const int64_t* __restrict__ cell,
@@ -200,39 +209,60 @@ __global__ void __launch_bounds__(256) k_adv_special(int nsp, const int64_t* __r
 }
 
 
-// The whole full-cell step in one pass over the box (3D): a block owns a
-// TX x TY column tile and marches up a chunk of ZC planes, keeping five planes
-// of n and of the cell class (k - 1 .. k + 3, with a two-cell x/y halo) in an
-// LDS ring. At plane k each thread takes its cell's slopes at k + 1 (carried
-// to the next step), publishes the extrapolation bases and normal slopes of
-// its cell at k for the x and y faces, the halo threads add those of the
-// cells just outside the tile, and then every thread forms the six face
-// fluxes of its cell (the z faces from its own column: the low one is the
-// previous step's high one), its conservative divergence and n_out. The
-// ring plane k + 4 and the own column's face velocities at k + 2 are loaded
-// a step before they are needed, so their latency overlaps a step of
-// arithmetic (the halo cells' few velocities are loaded in the step); the
-// register budget is held to four waves per SIMD. Cut cells (class 2) only get their
-// face fluxes stored (the cut-cell launches finish them); cells of class 2
-// or 3 store all six fluxes into F for the cut-cell forms, class 3 also its
-// D^c. Per face the arithmetic is that of adv_face_flux, up to contraction
-// of the transverse sums.
-template <int TX, int TY, int ZC>
-__global__ void __launch_bounds__(TX * TY, 2) k_adv_zm(const double* __restrict__ n, const uint8_t* __restrict__ cls,
+// value of the lane below / above (0 in lane 0 / 63)
+__device__ __forceinline__ double lane_below(double v) {
+  const long long b = __double_as_longlong(v);
+  const int l = __builtin_amdgcn_mov_dpp((int)b, 0x138, 0xf, 0xf, true);   // wavefront shift right by one
+  const int h = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x138, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
+__device__ __forceinline__ double lane_above(double v) {
+  const long long b = __double_as_longlong(v);
+  const int l = __builtin_amdgcn_mov_dpp((int)b, 0x130, 0xf, 0xf, true);   // wavefront shift left by one
+  const int h = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x130, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)h << 32) | (unsigned)l);
+}
+// entry at byte offset o (scalar base, 32-bit lane offset)
+template <typename T>
+__device__ __forceinline__ T& at(T* p, unsigned o) {
+  return *(T*)((const char*)p + o);
+}
+
+// The whole full-cell step in one pass over the box (3D): a wavefront holds
+// 64 consecutive cells of a row, a block R rows, and marches up ZC planes with
+// each lane's own column in registers. Lanes 2 .. 61 of rows 1 .. R - 2 are
+// the tile, the others its halo, which the same instructions compute: at plane
+// k every lane forms its cell's slopes and extrapolation bases (x neighbours
+// from the lanes beside it, y neighbours' densities and the bases and slopes
+// of the row below through LDS), then the fluxes of its cell's three low
+// faces, the upwind side chosen by selects. A cell's high x flux is the next
+// lane's low one; its divergence is closed one plane later, when the low z
+// flux above it and, through LDS, the low y flux of the next row are there:
+// each face is computed once and one barrier per plane suffices (every LDS
+// array alternates between two buffers).
+// Cells without gas hold NaN in the difference operands, which adv_mc turns
+// into the zero slope of the rule; their own fluxes are 0 by their class.
+// Cut cells (class 2) only get their face fluxes stored (the cut-cell launches
+// finish them); cells of class 2 or 3 store all six into F for the cut-cell
+// forms, class 3 also its D^c. Per face the arithmetic is that of
+// adv_face_flux, up to contraction of the transverse sums.
+// Bound by instruction issue (163 vector instructions a wavefront and plane,
+// 57 % of the launch's cycles at four wavefronts a SIMD) and the loads'
+// latency. A form with 16 x 16-cell tiles, whose threads each computed both
+// faces of two axes in branches and one wavefront of four the halo, took
+// 333 us for 256^3 cells (2.1 TB/s of the 41 B per cell); this one 195 us
+// (3.5 TB/s). Unrolled over the roles of the carried planes, without their
+// moves, it spilled 75 registers and took 465 us.
+template <int R, int ZC>
+__global__ void __launch_bounds__(64 * R) k_adv_rows(const double* __restrict__ n, const uint8_t* __restrict__ cls,
                                                     AdvVel vel, AdvGrid G, int tiles_x, int tiles_y,
                                                     double* __restrict__ F, double* __restrict__ Dc,
                                                     double* __restrict__ nout) {
-  constexpr int RX = TX + 4, RY = TY + 4, RP = RX * RY, NT = TX * TY;
-  constexpr int NR = (RP + NT - 1) / NT;   // ring elements per thread and plane
-  constexpr int NH = 2 * TY + 2 * TX;      // halo cells
-  static_assert(NH <= NT, "one halo cell per thread");
-  __shared__ double rn[5][RP];
-  __shared__ uint8_t rc[5][RP];
-  // per step parity: columns i0 - 1 .. i0 + TX of the tile's rows (x faces),
-  // rows j0 - 1 .. j0 + TY of its columns (y faces)
-  __shared__ double bx[2][TY][TX + 2], sxs[2][TY][TX + 2];
-  __shared__ double by[2][TY + 2][TX], sys[2][TY + 2][TX];
-  // every array offset fits in 32 bits (checked by the host)
+  __shared__ double ln[2][R + 2][64];              // densities of the rows and of the one on either side
+  __shared__ double lb[2][R][64], ls[2][R][64];    // y-face bases and slopes
+  __shared__ double lf[2][R][64];                  // low y fluxes
+  __shared__ unsigned long long lg[2][R];          // gas lanes of a row
+  // byte offsets within the block's planes fit in 32 bits (checked by the host)
   const int nx = G.n[0], ny = G.n[1], nz = G.n[2];
   const unsigned sxy = (unsigned)nx * ny;              // plane stride of cells and z faces
   const unsigned sfx = (unsigned)(nx + 1) * ny;        // plane stride of x faces
@@ -240,245 +270,188 @@ __global__ void __launch_bounds__(TX * TY, 2) k_adv_zm(const double* __restrict_
   const int64_t t = xcd_block(blockIdx.x, gridDim.x);
   const int tpc = tiles_x * tiles_y;
   const int zc = (int)(t / tpc), r = (int)(t % tpc);
-  const int i0 = (r % tiles_x) * TX, j0 = (r / tiles_x) * TY;
+  const int i0 = (r % tiles_x) * kAdvX, j0 = (r / tiles_x) * (R - 2);
   const int z0 = zc * ZC, z1 = min(nz, z0 + ZC);
-  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-  const int i = i0 + tx, j = j0 + ty;
-  const bool own = i < nx && j < ny;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int i = i0 - 2 + lane, j = j0 - 1 + w;
+  const bool in = i >= 0 && i < nx && j >= 0 && j < ny;
+  const bool out = lane >= 2 && lane < 2 + kAdvX && w >= 1 && w < R - 1 && in;
   const double h = G.h, dt = G.dt, c1 = 0.5 * dt / h, c2 = dt / (2.0 * h), rh = 1.0 / h;
-  const double* __restrict__ ux = vel.u[0];
-  const double* __restrict__ uy = vel.u[1];
-  const double* __restrict__ uz = vel.u[2];
-  // in-plane offsets: of the ring elements this thread fetches (-1: no cell),
-  // of the own cell's low x, y and z faces and cell
-  int roff[NR];
-#pragma unroll
-  for (int q = 0; q < NR; ++q) {
-    const int e = threadIdx.x + q * NT;
-    const int gi = i0 - 2 + e % RX, gj = j0 - 2 + e / RX;
-    roff[q] = (e < RP && gi >= 0 && gi < nx && gj >= 0 && gj < ny) ? gi + nx * gj : -1;
-  }
-  const unsigned ofx = (unsigned)i + (unsigned)(nx + 1) * j, ofy = (unsigned)i + (unsigned)nx * j;
-  const unsigned oc = ofy;   // cells and z faces share the in-plane layout
-  // ring plane k: fetched into registers one step ahead, stored later. The
-  // class and the density are requested together (a lane outside the box
-  // reads cell 0 and discards it), and the rule "no gas: NaN" is applied
-  // when the plane is stored, so no load waits for another.
-  double pv[NR];
-  uint8_t pc[NR];
-  uint32_t pin = 0;   // bit q: element q lies in the box and in a plane of it
-  auto fetch_plane = [&](int k) {
-    const bool kin = k >= 0 && k < nz;
-    const double* __restrict__ pn = n + (kin ? (int64_t)sxy * k : 0);
-    const uint8_t* __restrict__ pcl = cls + (kin ? (int64_t)sxy * k : 0);
-    pin = 0;
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      const unsigned o = roff[q] >= 0 ? (unsigned)roff[q] : 0u;
-      pc[q] = pcl[o];
-      pv[q] = pn[o];
-      pin |= (uint32_t)(kin && roff[q] >= 0) << q;
+  // the arrays from the block's first plane on
+  const int zb = max(z0 - 2, 0);
+  const double* __restrict__ nb = n + (int64_t)sxy * zb;
+  const uint8_t* __restrict__ clsb = cls + (int64_t)sxy * zb;
+  const double* __restrict__ ux = vel.u[0] + (int64_t)sfx * zb;
+  const double* __restrict__ uy = vel.u[1] + (int64_t)sfy * zb;
+  const double* __restrict__ uz = vel.u[2] + (int64_t)sxy * zb;
+  double* __restrict__ nob = nout + (int64_t)sxy * zb;
+  double* __restrict__ Dcb = Dc + (int64_t)sxy * zb;
+  double* __restrict__ Fx = F + G.fbase[0] + (int64_t)sfx * zb;
+  double* __restrict__ Fy = F + G.fbase[1] + (int64_t)sfy * zb;
+  double* __restrict__ Fz = F + G.fbase[2] + (int64_t)sxy * zb;
+  // in-plane offsets, clamped into the arrays: of the cell, its low x face
+  // (one past the box too), its low y face and the next row's
+  auto clamp = [](int v, int hi) { return (unsigned)min(max(v, 0), hi); };
+  const unsigned oc = clamp(i, nx - 1) + (unsigned)nx * clamp(j, ny - 1);
+  const unsigned ox = clamp(i, nx) + (unsigned)(nx + 1) * clamp(j, ny - 1);
+  const unsigned oy = clamp(i, nx - 1) + (unsigned)nx * clamp(j, ny);
+  const unsigned oyh = clamp(i, nx - 1) + (unsigned)nx * clamp(j + 1, ny);
+  // the row beyond the block that the first and the last row difference with
+  const bool outer = w == 0 || w == R - 1;
+  const int jo = w == 0 ? j - 1 : j + 1;
+  const int wo = w == 0 ? 0 : R + 1;
+  const bool ino = i >= 0 && i < nx && jo >= 0 && jo < ny;
+  const unsigned oo = clamp(i, nx - 1) + (unsigned)nx * clamp(jo, ny - 1);
+  const double kNaN = __builtin_nan("");
+  const double inx0 = G.inflow[0], inx1 = G.inflow[1], iny0 = G.inflow[2], iny1 = G.inflow[3];
+  const double inz0 = G.inflow[4], inz1 = G.inflow[5];
+  const bool edge = i0 < 2 || i0 + kAdvX + 2 > nx || j0 < 1 || j0 + R - 1 > ny;
+  // requested densities and classes (of the outer row too) and low velocities
+  // of a plane; two requests of each are in flight, taken up two steps after
+  // they were issued (one step is shorter than a loaded memory's latency)
+  struct Den {
+    double v, o;
+    uint8_t c, oc;
+  };
+  struct Vlow {
+    double x, y, yh, zh;
+  };
+  auto load_n = [&](int k, Den& d) {
+    const unsigned p = sxy * (clamp(k, nz - 1) - zb);
+    d.v = at(nb, 8 * (p + oc));
+    d.c = at(clsb, p + oc);
+    if (outer) {
+      d.o = at(nb, 8 * (p + oo));
+      d.oc = at(clsb, p + oo);
     }
   };
-  auto slot = [](int k) { return (k + 5) % 5; };   // k >= -1
-  auto store_plane = [&](int k) {
-    const int sl = slot(k);
-#pragma unroll
-    for (int q = 0; q < NR; ++q) {
-      const int e = threadIdx.x + q * NT;
-      if (e < RP) {
-        const uint8_t c = ((pin >> q) & 1) ? pc[q] : (uint8_t)0;
-        rn[sl][e] = c ? pv[q] : __builtin_nan("");
-        rc[sl][e] = c;
-      }
-    }
+  auto load_u = [&](int k, Vlow& v) {
+    const unsigned kc = clamp(k, nz - 1) - zb;
+    v.x = at(ux, 8 * (sfx * kc + ox));
+    v.y = at(uy, 8 * (sfy * kc + oy));
+    v.yh = at(uy, 8 * (sfy * kc + oyh));
+    v.zh = at(uz, 8 * (sxy * (clamp(k + 1, nz) - zb) + oc));
   };
-  // monotonised-central slopes of ring cell e at plane k: the ring holds
-  // NaN where there is no gas (or no cell), and adv_mc returns 0 for a NaN
-  // difference, which is the rule of a slope without gas on both sides
-  auto slopes = [&](int k, int e, double& sx, double& sy, double& sz) {
-    const int sm = slot(k - 1), sc = slot(k), sp = slot(k + 1);
-    const double c = rn[sc][e];
-    sx = adv_mc(c - rn[sc][e - 1], rn[sc][e + 1] - c);
-    sy = adv_mc(c - rn[sc][e - RX], rn[sc][e + RX] - c);
-    sz = adv_mc(c - rn[sm][e], rn[sp][e] - c);
-  };
-  // this thread's halo cell (if any): columns i0 - 1 and i0 + TX of the
-  // tile's rows (x faces), rows j0 - 1 and j0 + TY of its columns (y faces)
-  const int hq = threadIdx.x;
-  const bool has_halo = hq < NH;
-  const bool isx = hq < 2 * TY;
-  const int hx = isx ? ((hq & 1) ? TX : -1) : (hq - 2 * TY) % TX;
-  const int hy = isx ? (hq >> 1) : (((hq - 2 * TY) / TX) ? TY : -1);
-  const int hgi = i0 + hx, hgj = j0 + hy;
-  const bool hin = has_halo && hgi >= 0 && hgi < nx && hgj >= 0 && hgj < ny;
-  const int he = (hy + 2) * RX + (hx + 2);
-  const unsigned hoz = hin ? (unsigned)hgi + (unsigned)nx * hgj : 0u;
-  const unsigned hot = hin ? (isx ? hoz : (unsigned)hgi + (unsigned)(nx + 1) * hgj) : 0u;
-  // halo velocities at a plane: the z faces, then the in-plane transverse faces
-  // (requested unconditionally, a plane past the box clamped to the last
-  // one and a lane without a halo cell reading face 0, so that the compiler
-  // counts every load and never waits for more than the value it needs)
-  auto fetch_halo = [&](int k, double& z0v, double& z1v, double& t0v, double& t1v) {
-    const int kk = k < nz ? k : nz - 1;
-    const double* __restrict__ pz = uz + (int64_t)sxy * kk;
-    z0v = pz[hoz];
-    z1v = pz[hoz + sxy];
-    const double* __restrict__ pt = isx ? uy + (int64_t)sfy * kk : ux + (int64_t)sfx * kk;
-    t0v = pt[hot];
-    t1v = pt[hot + (isx ? (unsigned)nx : 1u)];
-  };
-  // own column: face velocities of the cell at a plane (requested the same way)
-  const unsigned ofxo = own ? ofx : 0u, ofyo = own ? ofy : 0u, oco = own ? oc : 0u;
-  auto fetch_own = [&](int k, double& xl, double& xh, double& yl, double& yh, double& zh) {
-    const int kk = k < nz ? k : nz - 1;
-    const double* __restrict__ px = ux + (int64_t)sfx * kk;
-    const double* __restrict__ py = uy + (int64_t)sfy * kk;
-    const double* __restrict__ pz = uz + (int64_t)sxy * (kk + 1);
-    xl = px[ofxo];
-    xh = px[ofxo + 1];
-    yl = py[ofyo];
-    yh = py[ofyo + nx];
-    zh = pz[oco];
-  };
-  // inflow densities of the six domain faces, read once
-  const double in0 = G.inflow[0], in1 = G.inflow[1], in2 = G.inflow[2], in3 = G.inflow[3], in5 = G.inflow[5];
-  const int eo = (ty + 2) * RX + (tx + 2);
-  double hz0 = 0, hz1 = 0, ht0 = 0, ht1 = 0;       // halo velocities of plane k
-  double gz0 = 0, gz1 = 0, gt0 = 0, gt1 = 0;       // of plane k + 1 (requested a step ahead)
-  double cuxl = 0, cuxh = 0, cuyl = 0, cuyh = 0, cuzl = 0, cuzh = 0;   // plane k
-  double auxl = 0, auxh = 0, auyl = 0, auyh = 0, auzh = 0;             // plane k + 1
-  fetch_plane(z0 - 1);
-  store_plane(z0 - 1);
-  fetch_plane(z0);
-  store_plane(z0);
-  fetch_plane(z0 + 1);
-  store_plane(z0 + 1);
-  fetch_plane(z0 + 2);
-  store_plane(z0 + 2);
-  fetch_plane(z0 + 3);
-  fetch_own(z0, cuxl, cuxh, cuyl, cuyh, cuzh);
-  fetch_own(z0 + 1, auxl, auxh, auyl, auyh, auzh);
-  fetch_halo(z0, gz0, gz1, gt0, gt1);
-  double fzl = 0.0;
-  if (own) {
-    cuzl = uz[(int64_t)sxy * z0 + oc];
-    fzl = adv_face_flux<3, 2>(n, cls, vel, G, i, j, z0);
+  // class of a taken-up request for plane k (0 outside the box)
+  auto cls_of = [&](int k, const Den& d) { return in && k >= 0 && k < nz ? (int)d.c : 0; };
+  auto outer_of = [&](int k, const Den& d) { return ino && k >= 0 && k < nz && d.oc != 0 ? d.o : kNaN; };
+  // planes k - 1, k, k + 1 of the own column at k = z0 - 1
+  double nm, nc, np, no;
+  int cc, cp;
+  double vzl;   // low z face of plane k
+  Vlow v0, v1;
+  Den d0, d1;
+  {
+    Den a, b, c;
+    load_n(z0 - 2, a);
+    load_n(z0 - 1, b);
+    load_n(z0, c);
+    vzl = at(uz, 8 * (sxy * (clamp(z0 - 1, nz) - zb) + oc));
+    load_u(z0 - 1, v0);
+    load_n(z0 + 1, d0);
+    load_u(z0, v1);
+    load_n(z0 + 2, d1);
+    cc = cls_of(z0 - 1, b);
+    cp = cls_of(z0, c);
+    nm = cls_of(z0 - 2, a) ? a.v : kNaN;
+    nc = cc ? b.v : kNaN;
+    np = cp ? c.v : kNaN;
+    no = outer_of(z0, c);
+    if (outer) ln[(z0 - 1) & 1][wo][lane] = outer_of(z0 - 1, b);
+    ln[(z0 - 1) & 1][w + 1][lane] = nc;
   }
   __syncthreads();
-  double cn = 0, csx = 0, csy = 0, csz = 0;
-  bool cg = false;
-  if (own) {
-    slopes(z0, eo, csx, csy, csz);
-    cg = rc[slot(z0)][eo] != 0;
-    cn = cg ? rn[slot(z0)][eo] : 0.0;
-  }
-  double* __restrict__ Fx = F + G.fbase[0];
-  double* __restrict__ Fy = F + G.fbase[1];
-  double* __restrict__ Fz = F + G.fbase[2];
-  const int rrow = (ty + 2) * RX;
-  // one barrier per plane: the ring runs three planes ahead (a plane is
-  // stored a step before it is read) and the face bases alternate between
-  // two buffers
-  for (int k = z0; k < z1; ++k) {
+  // what a plane leaves to the next one: z base, slope and gas, the low fluxes
+  // and the density of the cell still open
+  struct Open {
+    double bz, sz, fxl, fxh, fyl, fzl, n;
+    bool gas;
+    int cls;
+  };
+  Open pr = {0, 0, 0, 0, 0, 0, 0, false, 0};
+  // plane k: v holds its velocities, d the request for plane k + 2
+  auto step = [&](int k, Vlow& v, Den& d) {
     const int pb = k & 1;
-    if (k + 3 <= z1 + 1) store_plane(k + 3);
-    if (k + 4 <= z1 + 1) fetch_plane(k + 4);
-    hz0 = gz0;
-    hz1 = gz1;
-    ht0 = gt0;
-    ht1 = gt1;
-    fetch_halo(k + 1, gz0, gz1, gt0, gt1);
-    const int sk = slot(k);
-    // the own cell at plane k + 1
-    double nn = 0, nsx = 0, nsy = 0, nsz = 0;
-    bool ng = false;
-    if (own && k + 1 < nz) {
-      slopes(k + 1, eo, nsx, nsy, nsz);
-      ng = rc[slot(k + 1)][eo] != 0;
-      nn = ng ? rn[slot(k + 1)][eo] : 0.0;
-    }
-    const double cvx = 0.5 * (cuxl + cuxh), cvy = 0.5 * (cuyl + cuyh), cvz = 0.5 * (cuzl + cuzh);
-    if (own) {
-      bx[pb][ty][tx + 1] = cn - c1 * (cvy * csy + cvz * csz);
-      sxs[pb][ty][tx + 1] = csx;
-      by[pb][ty + 1][tx] = cn - c1 * (cvx * csx + cvz * csz);
-      sys[pb][ty + 1][tx] = csy;
-    }
-    if (has_halo) {
-      double b = 0.0, sl = 0.0;
-      if (hin) {
-        double sx, sy, sz;
-        slopes(k, he, sx, sy, sz);
-        const double c = rn[sk][he];
-        const double vz = 0.5 * (hz0 + hz1), vt = 0.5 * (ht0 + ht1);
-        b = c - c1 * (vt * (isx ? sy : sx) + vz * sz);
-        sl = isx ? sx : sy;
-      }
-      if (isx) {
-        bx[pb][hy][hx + 1] = b;
-        sxs[pb][hy][hx + 1] = sl;
-      } else {
-        by[pb][hy + 1][hx] = b;
-        sys[pb][hy + 1][hx] = sl;
-      }
-    }
+    const double vx0 = v.x, vy0 = v.y, vzh = v.zh;
+    // slopes and bases at plane k
+    const bool gas = cc != 0;
+    const double yl = ln[pb][w][lane], yh = ln[pb][w + 2][lane];
+    const double xl = lane_below(nc), xh = lane_above(nc);
+    const double sx = adv_mc(nc - xl, xh - nc), sy = adv_mc(nc - yl, yh - nc), sz = adv_mc(nc - nm, np - nc);
+    const double vx = 0.5 * (vx0 + lane_above(vx0)), vy = 0.5 * (vy0 + v.yh), vz = 0.5 * (vzl + vzh);
+    // NaN in cells without gas, whose fluxes are not used
+    const double bx = nc - c1 * (vy * sy + vz * sz);
+    const double by = nc - c1 * (vx * sx + vz * sz);
+    const double bz = nc - c1 * (vx * sx + vy * sy);
+    const unsigned long long gm = __ballot(gas);
+    lb[pb][w][lane] = by;
+    ls[pb][w][lane] = sy;
+    if (lane == 0) lg[pb][w] = gm;
+    ln[pb ^ 1][w + 1][lane] = np;
+    if (outer) ln[pb ^ 1][wo][lane] = no;
+    load_u(k + 2, v);
     __syncthreads();
-    if (own) {
-      // x faces i (low) and i + 1 (high); region column c <-> cell i0 - 1 + c
-      auto xflux = [&](int f, double u) {
-        const bool up = u >= 0.0;
-        if (up ? f == 0 : f == nx) return u * (up ? in0 : in1);
-        const int col = f - i0 + (up ? 0 : 1);
-        if (!rc[sk][rrow + col + 1]) return 0.0;
-        return u * (bx[pb][ty][col] + ((up ? 0.5 : -0.5) - u * c2) * sxs[pb][ty][col]);
-      };
-      auto yflux = [&](int f, double u) {
-        const bool up = u >= 0.0;
-        if (up ? f == 0 : f == ny) return u * (up ? in2 : in3);
-        const int row = f - j0 + (up ? 0 : 1);
-        if (!rc[sk][(row + 1) * RX + tx + 2]) return 0.0;
-        return u * (by[pb][row][tx] + ((up ? 0.5 : -0.5) - u * c2) * sys[pb][row][tx]);
-      };
-      const double fxl = xflux(i, cuxl), fxh = xflux(i + 1, cuxh);
-      const double fyl = yflux(j, cuyl), fyh = yflux(j + 1, cuyh);
-      // z face k + 1: from the own cell at k (upwind from below) or at k + 1
-      double fzh;
-      {
-        const double u = cuzh;
-        const bool up = u >= 0.0;
-        if (!up && k + 1 == nz) {
-          fzh = u * in5;
-        } else if (up) {
-          fzh = cg ? u * ((cn - c1 * (cvx * csx + cvy * csy)) + (0.5 - u * c2) * csz) : 0.0;
-        } else {
-          const double nvx = 0.5 * (auxl + auxh), nvy = 0.5 * (auyl + auyh);
-          fzh = ng ? u * ((nn - c1 * (nvx * nsx + nvy * nsy)) + (-0.5 - u * c2) * nsz) : 0.0;
-        }
-      }
-      const unsigned q = oc + sxy * (unsigned)k;
-      const uint8_t tc = rc[sk][eo];
-      if (tc == 0) {
-        nout[q] = 0.0;
-      } else if (tc != 2) {
-        const double dc = ((fxh - fxl) + (fyh - fyl) + (fzh - fzl)) * rh;
-        if (tc == 3) Dc[q] = dc;
-        nout[q] = cn - dt * dc;
-      }
-      if (tc >= 2) {
-        const unsigned qx = ofx + sfx * (unsigned)k, qy = ofy + sfy * (unsigned)k;
-        Fx[qx] = fxl;
-        Fx[qx + 1] = fxh;
-        Fy[qy] = fyl;
-        Fy[qy + nx] = fyh;
-        Fz[q] = fzl;
-        Fz[q + sxy] = fzh;
-      }
-      fzl = fzh;
+    // low-face fluxes of plane k
+    auto face = [&](double u, bool g, double b, double s) {
+      const double f = u * (b + (__builtin_copysign(0.5, u) - u * c2) * s);
+      return g ? f : 0.0;
+    };
+    const int wd = max(w - 1, 0);
+    const unsigned long long gdv = lg[pb][wd];   // uniform: a lane's bit through a scalar mask
+    const unsigned long long gd =
+        ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(gdv >> 32)) << 32) |
+        (unsigned)__builtin_amdgcn_readfirstlane((int)gdv);
+    const bool gxd = __builtin_amdgcn_inverse_ballot_w64(gm << 1), gyd = __builtin_amdgcn_inverse_ballot_w64(gd);
+    const double byd = lb[pb][wd][lane], syd = ls[pb][wd][lane];
+    const double bxd = lane_below(bx), sxd = lane_below(sx);
+    const bool upx = vx0 >= 0.0, upy = vy0 >= 0.0, upz = vzl >= 0.0;
+    double fx = face(vx0, upx ? gxd : gas, upx ? bxd : bx, upx ? sxd : sx);
+    double fy = face(vy0, upy ? gyd : gas, upy ? byd : by, upy ? syd : sy);
+    double fz = face(vzl, upz ? pr.gas : gas, upz ? pr.bz : bz, upz ? pr.sz : sz);
+    if (edge) {   // inflow through the domain faces
+      if (i == 0 && upx) fx = vx0 * inx0;
+      if (i == nx && !upx) fx = vx0 * inx1;
+      if (j == 0 && upy) fy = vy0 * iny0;
+      if (j == ny && !upy) fy = vy0 * iny1;
     }
-    cn = nn; csx = nsx; csy = nsy; csz = nsz; cg = ng;
-    cuxl = auxl; cuxh = auxh; cuyl = auyl; cuyh = auyh; cuzl = cuzh; cuzh = auzh;
-    fetch_own(k + 2, auxl, auxh, auyl, auyh, auzh);
+    if (k == 0 && upz) fz = vzl * inz0;
+    if (k == nz && !upz) fz = vzl * inz1;
+    lf[pb][w][lane] = fy;
+    // close the cell of plane k - 1
+    if (out && k > z0) {
+      const double fyh = lf[pb ^ 1][w + 1][lane];
+      const unsigned q = 8 * (sxy * (k - 1 - zb) + oc);
+      if (pr.cls == 0) {
+        at(nob, q) = 0.0;
+      } else if (pr.cls != 2) {
+        const double dc = ((pr.fxh - pr.fxl) + (fyh - pr.fyl) + (fz - pr.fzl)) * rh;
+        if (pr.cls == 3) at(Dcb, q) = dc;
+        at(nob, q) = pr.n - dt * dc;
+      }
+      if (pr.cls >= 2) {
+        const unsigned qx = 8 * (sfx * (k - 1 - zb) + ox), qy = sfy * (k - 1 - zb);
+        at(Fx, qx) = pr.fxl;
+        at(Fx, qx + 8) = pr.fxh;
+        at(Fy, 8 * (qy + oy)) = pr.fyl;
+        at(Fy, 8 * (qy + oyh)) = fyh;
+        at(Fz, q) = pr.fzl;
+        at(Fz, q + 8 * sxy) = fz;
+      }
+    }
+    pr = {bz, sz, fx, lane_above(fx), fy, fz, nc, gas, cc};
+    cc = cp;
+    cp = cls_of(k + 2, d);
+    nm = nc;
+    nc = np;
+    np = cp ? d.v : kNaN;
+    if (outer) no = outer_of(k + 2, d);
+    load_n(k + 4, d);
+    vzl = vzh;
+  };
+  for (int k = z0 - 1; k <= z1; k += 2) {
+    step(k, v0, d0);
+    if (k < z1) step(k + 1, v1, d1);
   }
 }
 

@@ -4289,16 +4289,30 @@ ebmg_status ebmg_advect(ebmg_problem pb, const double* n_in, const double* u_x, 
     vel.u[2] = D == 3 ? u_z : u_x;
     auto flux_grid = [&](int d) { return dim3(nblk((int64_t)(g.n[0] + (d == 0)) * (g.n[1] + (d == 1)))); };
     const dim3 cell_grid(nblk((int64_t)g.n[0] * g.n[1]));
-    const bool off32 = (int64_t)(g.n[0] + 1) * (g.n[1] + 1) * (g.n[2] + 1) < ((int64_t)1 << 31);
-    if (D == 3 && off32) {
-      // one z-marching pass (its offsets are 32-bit)
-      constexpr int TX = 16, TY = 16, ZC = 32;
-      const int tiles_x = (g.n[0] + TX - 1) / TX, tiles_y = (g.n[1] + TY - 1) / TY;
-      const int64_t blocks = (int64_t)tiles_x * tiles_y * ((g.n[2] + ZC - 1) / ZC);
-      hipLaunchKernelGGL((k_adv_zm<TX, TY, ZC>), dim3((unsigned)blocks), dim3(TX * TY), 0, s, n_in, A.cls.p, vel, g,
-                         tiles_x, tiles_y, A.F.p, A.Dc.p, n_out);
+    // k_adv_rows<R, ZC>: 32-bit byte offsets over the ZC + 8 planes a block touches
+    auto rows_ok = [&](int ZC) {
+      return (int64_t)(g.n[0] + 1) * (g.n[1] + 1) * (ZC + 8) * (int64_t)sizeof(double) < ((int64_t)1 << 32) &&
+             (int64_t)(g.n[0] + 1) * (g.n[1] + 1) * (g.n[2] + 1) < ((int64_t)1 << 31);
+    };
+    auto rows_blocks = [&](int R, int ZC) {
+      return (int64_t)((g.n[0] + kAdvX - 1) / kAdvX) * ((g.n[1] + R - 3) / (R - 2)) * ((g.n[2] + ZC - 1) / ZC);
+    };
+    auto rows = [&](auto kernel, int R, int ZC) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)rows_blocks(R, ZC)), dim3(64 * R), 0, s, n_in, A.cls.p, vel, g,
+                         (g.n[0] + kAdvX - 1) / kAdvX, (g.n[1] + R - 3) / (R - 2), A.F.p, A.Dc.p, n_out);
+    };
+    // one z-marching pass: tall blocks of 16 rows waste the least (two halo
+    // rows of 16, two halo planes of 32) but fill the chip, one to a CU, only
+    // from two rounds of them on; below, small blocks (200^3: 162 against
+    // 163 us a step, 100^3: 89 against 51, 64^3: 86 against 42; 256^3: 240
+    // against 302)
+    if (D == 3 && rows_ok(32) && rows_blocks(16, 32) >= 512) {
+      rows(k_adv_rows<16, 32>, 16, 32);
+    } else if (D == 3 && rows_ok(8)) {
+      rows(k_adv_rows<8, 8>, 8, 8);
     } else if (D == 3) {
-      // boxes of 2^31 faces or more: face fluxes, then the full cells
+      // boxes of 2^31 faces or more, or planes too large for the offsets: face
+      // fluxes, then the full cells
       for (int d = 0; d < 3; ++d) {
         const dim3 grid(nblk((int64_t)(g.n[0] + (d == 0)) * (g.n[1] + (d == 1))), (unsigned)(g.n[2] + (d == 2)));
         auto k = d == 0 ? k_adv_flux<3, 0> : (d == 1 ? k_adv_flux<3, 1> : k_adv_flux<3, 2>);
@@ -4312,9 +4326,9 @@ ebmg_status ebmg_advect(ebmg_problem pb, const double* n_in, const double* u_x, 
       hipLaunchKernelGGL(k_adv_full<2>, cell_grid, dim3(256), 0, s, A.cls.p, g, A.F.p, n_in, A.Dc.p, n_out);
     }
     if (A.ncut > 0) {
-      hipLaunchKernelGGL(k_adv_dc_cut, dim3(nblk(A.ncut)), dim3(256), 0, s, A.ncut, A.cut_cell.p, A.dc_ptr.p,
+      hipLaunchKernelGGL(k_adv_dc_cut, dim3(nblk_sub(A.ncut)), dim3(256), 0, s, A.ncut, A.cut_cell.p, A.dc_ptr.p,
                          A.dc_face.p, A.dc_coef.p, A.F.p, A.Dc.p);
-      hipLaunchKernelGGL(k_adv_cut, dim3(nblk(A.ncut)), dim3(256), 0, s, A.ncut, A.cut_cell.p, A.kappa.p, A.nb_ptr.p,
+      hipLaunchKernelGGL(k_adv_cut, dim3(nblk_sub(A.ncut)), dim3(256), 0, s, A.ncut, A.cut_cell.p, A.kappa.p, A.nb_ptr.p,
                          A.nb_cell.p, A.nb_w.p, A.cut_S.p, A.Dc.p, A.Dcut.p, A.give.p);
     }
     if (A.nsp > 0)
