@@ -522,29 +522,36 @@ __global__ void __launch_bounds__(kRowBlock) k_irr_jac_sl2x(BLev<T> L, int nb1, 
 // take group 0, the rest group 1 (kSplitRows rows per block). x may be
 // narrower than T; NDOT >= 1 adds da[q] * r[q] and NDOT == 2 also r[q]^2 over
 // the rows, one partial per block at part[d * pt + boff + block].
-template <typename T, int MODE, typename TX = T, int NDOT = 0>
+// TWO: the unknowns from nx on are read from x2 and written to r2 (a caller's
+// second-phase arrays).
+template <typename T, int MODE, typename TX = T, int NDOT = 0, bool TWO = false>
 __global__ void __launch_bounds__(kRowBlock) k_resid_irr_sl(BLev<T> L, int nb0, const TX* __restrict__ x,
                                                          const T* __restrict__ b, T* __restrict__ r,
                                                          const double* __restrict__ da = nullptr,
                                                          double* __restrict__ part = nullptr, int64_t pt = 0,
-                                                         int64_t boff = 0) {
+                                                         int64_t boff = 0, const TX* __restrict__ x2 = nullptr,
+                                                         T* __restrict__ r2 = nullptr, int nx = 0) {
   FP_EXACT_ORDER
   double a0 = 0, a1 = 0;
   const int grp = (int)blockIdx.x < nb0 ? 0 : 1;
   const int blk = grp == 0 ? (int)blockIdx.x : (int)blockIdx.x - nb0;
-  split_rows<T, TX, false>(
+  split_rows<T, TX, TWO>(
       L, grp, x, blk,
       [&](int g) {
         const int64_t q = L.irow_dof[g];
-        return RowOwn<T>{q, L.diag[g], (T)x[q]};
+        return RowOwn<T>{q, L.diag[g], TWO && q >= nx ? (T)x2[q - nx] : (T)x[q]};
       },
       [&](int g, const RowOwn<T>& w, T sm) {
         const T ax = w.d * w.v + sm;
         const T o = MODE == 0 ? b[w.q] - ax : ax;
-        r[w.q] = o;
+        if (TWO && w.q >= nx)
+          r2[w.q - nx] = o;
+        else
+          r[w.q] = o;
         if (NDOT >= 1) a0 += da[w.q] * (double)o;
         if (NDOT == 2) a1 += (double)o * (double)o;
-      });
+      },
+      x2, nx);
   if (NDOT > 0) block_partials<kRowBlock>(a0, a1, NDOT, part, pt, boff + blockIdx.x, threadIdx.x);
 }
 

@@ -1510,14 +1510,17 @@ __global__ void __launch_bounds__(kBlock) k_prolong_q(const uint8_t* __restrict_
 // and covered cells (MODE as in k_resid_reg), the rest the explicit rows with
 // kSub lanes each (as k_resid_irr); TX and NDOT as in k_resid_zm3, with one
 // partial per block of this launch.
-template <typename T, int DIM, int MODE, typename TX = T, int NDOT = 0>
+// TWO: the second-phase unknowns are read from x2 and written to r2.
+template <typename T, int DIM, int MODE, typename TX = T, int NDOT = 0, bool TWO = false>
 __global__ void __launch_bounds__(kBlock) k_resid_all(const uint8_t* __restrict__ tag, const TX* __restrict__ x,
                                                       const T* __restrict__ b, T* __restrict__ r, Tmpl<T> tp,
                                                       unsigned nbc, int nrows, const int64_t* __restrict__ dof,
                                                       const int64_t* __restrict__ rp,
                                                       const int32_t* __restrict__ col, const T* __restrict__ val,
                                                       const T* __restrict__ diag, const T* __restrict__ da = nullptr,
-                                                      double* __restrict__ part = nullptr, int64_t pt = 0) {
+                                                      double* __restrict__ part = nullptr, int64_t pt = 0,
+                                                      const TX* __restrict__ x2 = nullptr,
+                                                      T* __restrict__ r2 = nullptr) {
   double d0 = 0, d1 = 0;
   if (blockIdx.x < nbc) {
     const int nx = tp.n[0], ny = tp.n[1];
@@ -1561,13 +1564,18 @@ __global__ void __launch_bounds__(kBlock) k_resid_all(const uint8_t* __restrict_
     const int lane = threadIdx.x % kSub;
     if (g < nrows) {
       const int64_t q = dof[g];
+      const int64_t N = (int64_t)tp.n[0] * tp.n[1] * (DIM == 3 ? tp.n[2] : 1);
+      auto ld = [&](int64_t c) { return TWO && c >= N ? (T)x2[c - N] : (T)x[c]; };
       T s = 0;
-      for (int64_t e = rp[g] + lane; e < rp[g + 1]; e += kSub) s += val[e] * (T)x[col[e]];
+      for (int64_t e = rp[g] + lane; e < rp[g + 1]; e += kSub) s += val[e] * ld(col[e]);
       for (int off = kSub / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kSub);
       if (lane == 0) {
-        const T ax = diag[g] * (T)x[q] + s;
+        const T ax = diag[g] * ld(q) + s;
         const T out = MODE == 0 ? b[q] - ax : ax;
-        r[q] = out;
+        if (TWO && q >= N)
+          r2[q - N] = out;
+        else
+          r[q] = out;
         if (NDOT > 0) {
           d0 = (double)da[q] * (double)out;
           if (NDOT > 1) d1 = (double)out * (double)out;
@@ -1864,14 +1872,21 @@ __global__ void __launch_bounds__(kBlock) k_rhs_reg(const uint8_t* __restrict__ 
 struct FaceVals {
   double v[6];
 };
+// the objects' values of a solve, as a kernel argument (up to kMaxObj of
+// them, else in device memory)
+constexpr int kMaxObj = 64;
+struct ObjVals {
+  const double* p;
+  double v[kMaxObj];
+  __device__ __forceinline__ double operator[](int k) const { return p ? p[k] : v[k]; }
+};
 
 __global__ void __launch_bounds__(kBlock) k_rhs_irr(int nrows, const int64_t* __restrict__ dof,
                                                     const int64_t* __restrict__ cell, const double* __restrict__ src,
                                                     const double* __restrict__ cface, const int32_t* __restrict__ obj,
                                                     const double* __restrict__ cobj, const double* __restrict__ csig,
                                                     const double* __restrict__ rho, const double* __restrict__ sigma,
-                                                    const double* __restrict__ objv, FaceVals fv,
-                                                    double* __restrict__ b) {
+                                                    ObjVals objv, FaceVals fv, double* __restrict__ b) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nrows) return;
   const int64_t c = cell[t];
@@ -1985,8 +2000,8 @@ __global__ void __launch_bounds__(kBlock) k_efield_irr(int ncell, int dim, int64
                                                        const double* __restrict__ val, const double* __restrict__ cface,
                                                        const int32_t* __restrict__ obj, const double* __restrict__ cobj,
                                                        const double* __restrict__ csig, const double* __restrict__ x,
-                                                       const double* __restrict__ sigma,
-                                                       const double* __restrict__ objv, FaceVals fv,
+                                                       const double* __restrict__ x2,
+                                                       const double* __restrict__ sigma, ObjVals objv, FaceVals fv,
                                                        double* __restrict__ E) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= ncell * dim) return;
@@ -1994,7 +2009,7 @@ __global__ void __launch_bounds__(kBlock) k_efield_irr(int ncell, int dim, int64
   const int e = 3 * q + d;
   const int64_t c = ecell[q];
   double v = 0;
-  for (int64_t z = rp[e]; z < rp[e + 1]; ++z) v += val[z] * x[col[z]];
+  for (int64_t z = rp[e]; z < rp[e + 1]; ++z) v += val[z] * (col[z] < N ? x[col[z]] : x2[col[z] - N]);
   for (int f = 0; f < 6; ++f) v += cface[6 * e + f] * fv.v[f];
   if (obj[e] >= 0) v += cobj[e] * objv[obj[e]];
   if (sigma) v += csig[e] * sigma[c];

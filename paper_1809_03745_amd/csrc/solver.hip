@@ -1497,6 +1497,41 @@ static void residual(DevLevel& l, const T* x, const T* b, T* r, hipStream_t s) {
   HIPCHECK(hipGetLastError());
 }
 
+// out = A [x; x2] on the finest level straight from and into a caller's
+// arrays (which do not overlap): the kernels, and the results, of
+// residual<double, 1>.
+static void apply_split(DevLevel& l, const double* x, const double* x2, double* out, double* out2, hipStream_t s) {
+  const Tmpl<double>& tp = l.t64;
+  const double* none = nullptr;
+  if (l.dim == 3 && l.N >= kResidZMMin) {
+    if (pair_ok(l) && al2(x) && al2(out))
+      hipLaunchKernelGGL((k_resid_zp3<double, 1>), dim3((unsigned)zp_resid_blocks(l)), dim3(64, kRPY), 0, s, l.tag.p, x,
+                         none, out, tp, none, (double*)nullptr, (int64_t)0);
+    else
+      hipLaunchKernelGGL((k_resid_zm3<double, 1>), dim3((unsigned)zm_resid_blocks(l)), dim3(kRZX, kRZY), 0, s, l.tag.p,
+                         x, none, out, tp, none, (double*)nullptr, (int64_t)0);
+    if (l.R > 0) {
+      const BLev<double> L = make_blev<double>(l);
+      const int nb0 = (L.grp_ptr[1] - L.grp_ptr[0] + kSplitRows - 1) / kSplitRows;
+      const int nb1 = (L.grp_ptr[2] - L.grp_ptr[1] + kSplitRows - 1) / kSplitRows;
+      hipLaunchKernelGGL((k_resid_irr_sl<double, 1, double, 0, true>), dim3((unsigned)(nb0 + nb1)), dim3(kRowBlock), 0,
+                         s, L, nb0, x, none, out, none, (double*)nullptr, (int64_t)0, (int64_t)0, x2, out2, (int)l.N);
+    }
+  } else {
+    const unsigned nbc = nblk(l.N);
+    auto* k = l.dim == 3 ? k_resid_all<double, 3, 1, double, 0, true> : k_resid_all<double, 2, 1, double, 0, true>;
+    hipLaunchKernelGGL(k, dim3(nbc + nblk(l.R * kSub)), dim3(kBlock), 0, s, l.tag.p, x, none, out, tp, nbc, (int)l.R,
+                       l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, none, (double*)nullptr, (int64_t)0, x2,
+                       out2);
+  }
+  HIPCHECK(hipGetLastError());
+}
+
+// whether the arrays a[0, na) and b[0, nb) (either may be null) share memory
+static bool overlap(const double* a, int64_t na, const double* b, int64_t nb) {
+  return a && b && a < b + nb && b < a + na;
+}
+
 // restriction of rf into the coarse right-hand side bc, clearing the coarse
 // correction xc, in one launch
 template <typename T>
@@ -1760,6 +1795,22 @@ static double norm2(DevProblem& D, const T* r, int64_t n, hipStream_t s) {
   return std::sqrt(D.host_scal[SC_RR]);
 }
 
+// the objects' values: a call's, or the setup's
+static ObjVals object_values(ebmg_problem_s* P, const double* objv) {
+  const std::vector<double>& setup = P->host->geo.obj_value;
+  const double* v = objv ? objv : setup.data();
+  ObjVals o;
+  std::memset(&o, 0, sizeof(o));
+  if (setup.size() <= (size_t)kMaxObj) {
+    std::copy(v, v + setup.size(), o.v);
+  } else {
+    o.p = P->dev.objv.p;
+    HIPCHECK(hipMemcpyAsync(P->dev.objv.p, v, sizeof(double) * setup.size(), hipMemcpyHostToDevice, P->ctx->stream));
+    HIPCHECK(hipStreamSynchronize(P->ctx->stream));   // v may not outlive the copy
+  }
+  return o;
+}
+
 static void rhs(ebmg_problem_s* P, const double* rho, const double* sigma, const double* bcv, const double* objv) {
   Problem& H = *P->host;
   DevProblem& D = P->dev;
@@ -1767,10 +1818,7 @@ static void rhs(ebmg_problem_s* P, const double* rho, const double* sigma, const
   hipStream_t s = P->ctx->stream;
   FaceVals fv;
   for (int f = 0; f < 6; ++f) fv.v[f] = bcv ? bcv[f] : H.bc.value[f];
-  const size_t no = H.geo.obj_value.size();
-  std::vector<double> ov(std::max<size_t>(1, no), 0.0);
-  for (size_t k = 0; k < no; ++k) ov[k] = objv ? objv[k] : H.geo.obj_value[k];
-  HIPCHECK(hipMemcpyAsync(D.objv.p, ov.data(), sizeof(double) * ov.size(), hipMemcpyHostToDevice, s));
+  const ObjVals ov = object_values(P, objv);
   Tmpl<double> dat;
   for (int d = 0; d < 3; ++d) dat.n[d] = L.n[d];
   for (int f = 0; f < 6; ++f)
@@ -1782,13 +1830,13 @@ static void rhs(ebmg_problem_s* P, const double* rho, const double* sigma, const
     hipLaunchKernelGGL((k_rhs_reg<2>), sh.g, sh.b, 0, s, L.tag.p, rho, L.b64.p, dat, 0);
   if (L.R > 0)
     hipLaunchKernelGGL(k_rhs_irr, dim3(nblk(L.R)), dim3(kBlock), 0, s, (int)L.R, L.irow_dof.p, D.icell.p, D.isrc.p,
-                       D.iface.p, D.iobj.p, D.icobj.p, D.icsig.p, rho, sigma, D.objv.p, fv, L.b64.p);
+                       D.iface.p, D.iobj.p, D.icobj.p, D.icsig.p, rho, sigma, ov, fv, L.b64.p);
   HIPCHECK(hipGetLastError());
-  // the host copy of ov must outlive the async copy
-  HIPCHECK(hipStreamSynchronize(s));
 }
 
-static void efield(ebmg_problem_s* P, const double* x, const double* sigma, const double* bcv, double* E) {
+// x: the cells' values, x2: the second-phase unknowns'
+static void efield(ebmg_problem_s* P, const double* x, const double* x2, const double* sigma, const double* bcv,
+                   const double* objv, double* E) {
   Problem& H = *P->host;
   DevProblem& D = P->dev;
   DevLevel& L = D.lv[0];
@@ -1816,8 +1864,8 @@ static void efield(ebmg_problem_s* P, const double* x, const double* sigma, cons
   const int nc = (int)H.fine.ecell.size();
   if (nc > 0)
     hipLaunchKernelGGL(k_efield_irr, dim3(nblk((int64_t)nc * L.dim)), dim3(kBlock), 0, s, nc, L.dim, L.N, D.ecell.p,
-                       D.erp.p, D.ecol.p, D.eval.p, D.eface.p, D.eobj.p, D.ecobj.p, D.ecsig.p, x, sigma, D.objv.p,
-                       fv, E);
+                       D.erp.p, D.ecol.p, D.eval.p, D.eface.p, D.eobj.p, D.ecobj.p, D.ecsig.p, x, x2,
+                       sigma, object_values(P, objv), fv, E);
   HIPCHECK(hipGetLastError());
 }
 
@@ -2087,7 +2135,7 @@ static ebmg_status solve(ebmg_problem_s* P, const double* rho, const double* sig
   HIPCHECK(hipMemcpyAsync(phi, L.x64.p, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
   if (phi2 && L.N2 > 0)
     HIPCHECK(hipMemcpyAsync(phi2, L.x64.p + L.N, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
-  if (E) efield(P, L.x64.p, sigma, bcv, E);
+  if (E) efield(P, L.x64.p, L.x64.p + L.N, sigma, bcv, objv, E);
   HIPCHECK(hipStreamSynchronize(s));
   for (auto& k : D.kt)
     if (k) k->harvest();
@@ -3381,14 +3429,21 @@ ebmg_status ebmg_apply(ebmg_problem pb, const double* phi, const double* phi2, d
     HIPCHECK(hipSetDevice(pb->ctx->device));
     DevLevel& L = pb->dev.lv[0];
     hipStream_t s = pb->ctx->stream;
-    HIPCHECK(hipMemcpyAsync(L.x64.p, phi, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
-    if (L.N2 > 0) {
-      if (!phi2 || !out2) throw ArgError("second-phase arrays required");
-      HIPCHECK(hipMemcpyAsync(L.x64.p + L.N, phi2, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
+    if (L.N2 > 0 && (!phi2 || !out2)) throw ArgError("second-phase arrays required");
+    const bool in_place = overlap(phi, L.N, out, L.N) || overlap(phi, L.N, out2, L.N2) ||
+                          overlap(phi2, L.N2, out, L.N) || overlap(phi2, L.N2, out2, L.N2);
+    if (!in_place) {
+      apply_split(L, phi, phi2, out, out2, s);
+    } else {
+      // input and output share memory: staged through the level's vectors
+      HIPCHECK(hipMemcpyAsync(L.x64.p, phi, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
+      if (L.N2 > 0)
+        HIPCHECK(hipMemcpyAsync(L.x64.p + L.N, phi2, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
+      residual<double, 1>(L, L.x64.p, nullptr, L.r64.p, s);
+      HIPCHECK(hipMemcpyAsync(out, L.r64.p, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
+      if (L.N2 > 0)
+        HIPCHECK(hipMemcpyAsync(out2, L.r64.p + L.N, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
     }
-    residual<double, 1>(L, L.x64.p, nullptr, L.r64.p, s);
-    HIPCHECK(hipMemcpyAsync(out, L.r64.p, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
-    if (L.N2 > 0) HIPCHECK(hipMemcpyAsync(out2, L.r64.p + L.N, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
     HIPCHECK(hipStreamSynchronize(s));
     return EBMG_OK;
   });
@@ -3430,20 +3485,19 @@ ebmg_status ebmg_efield(ebmg_problem pb, const double* phi, const double* phi2, 
   return guard(pb->ctx, [&]() -> ebmg_status {
     drain(pb);
     HIPCHECK(hipSetDevice(pb->ctx->device));
-    DevProblem& D = pb->dev;
-    DevLevel& L = D.lv[0];
+    DevLevel& L = pb->dev.lv[0];
     hipStream_t s = pb->ctx->stream;
-    const Problem& H = *pb->host;
-    const size_t no = H.geo.obj_value.size();
-    std::vector<double> ov(std::max<size_t>(1, no), 0.0);
-    for (size_t k = 0; k < no; ++k) ov[k] = objv ? objv[k] : H.geo.obj_value[k];
-    HIPCHECK(hipMemcpyAsync(D.objv.p, ov.data(), sizeof(double) * ov.size(), hipMemcpyHostToDevice, s));
-    HIPCHECK(hipMemcpyAsync(L.x64.p, phi, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
-    if (L.N2 > 0) {
-      if (!phi2) throw ArgError("second-phase array required");
-      HIPCHECK(hipMemcpyAsync(L.x64.p + L.N, phi2, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
+    if (L.N2 > 0 && !phi2) throw ArgError("second-phase array required");
+    const int64_t ne = (int64_t)L.dim * L.N;
+    if (!overlap(phi, L.N, E, ne) && !overlap(phi2, L.N2, E, ne)) {
+      efield(pb, phi, phi2, sigma, bcv, objv, E);
+    } else {
+      // E shares memory with phi: the input staged through the level's vector
+      HIPCHECK(hipMemcpyAsync(L.x64.p, phi, sizeof(double) * L.N, hipMemcpyDeviceToDevice, s));
+      if (L.N2 > 0)
+        HIPCHECK(hipMemcpyAsync(L.x64.p + L.N, phi2, sizeof(double) * L.N2, hipMemcpyDeviceToDevice, s));
+      efield(pb, L.x64.p, L.x64.p + L.N, sigma, bcv, objv, E);
     }
-    efield(pb, L.x64.p, sigma, bcv, E);
     HIPCHECK(hipStreamSynchronize(s));
     return EBMG_OK;
   });
