@@ -449,7 +449,7 @@ __device__ __forceinline__ T zm_inplane_rdg(int gx, int gy, int nx, int ny, cons
 template <typename T, int TX, int TY, int KZ, bool WIDE = false, bool ZIN = false>
 __global__ void __launch_bounds__(TX * TY / 2) k_rb_zm3(const uint8_t* __restrict__ tag,
                                                       const T* __restrict__ xin, T* __restrict__ xout,
-                                                      const T* __restrict__ b, Tmpl<T> tp, int64_t nsec) {
+                                                      const T* __restrict__ b, Tmpl<T> tp, int64_t nsec, int kz) {
   constexpr int NT = TX * TY / 2;
   constexpr int OX = TX + 4, OY = TY + 4, NO = OX * OY;      // old-value halo region
   constexpr int RX = TX + 2, RY = TY + 2, NR = RX * RY;      // red ring region
@@ -479,8 +479,8 @@ __global__ void __launch_bounds__(TX * TY / 2) k_rb_zm3(const uint8_t* __restric
   const int64_t nblocks = (int64_t)gridDim.x;
   const int64_t t = xcd_block(blockIdx.x, nblocks);
   const int x0 = (int)(t % bx) * TX, y0 = (int)((t / bx) % by) * TY;
-  const int z0 = (int)(t / ((int64_t)bx * by)) * KZ;
-  const int z1 = min(z0 + KZ, nz);
+  const int z0 = (int)(t / ((int64_t)bx * by)) * kz;   // kz: KZ, or fewer on small levels
+  const int z1 = min(z0 + kz, nz);
   const int tid = threadIdx.x;
   const int stid = NT - 1 - tid;   // staging lane (reversed)
   const int64_t sxy = (int64_t)nx * ny;
@@ -1046,7 +1046,7 @@ template <typename T, int MODE, typename TX = T, int NDOT = 0>
 __global__ void __launch_bounds__(kRZX * kRZY) k_resid_zm3(const uint8_t* __restrict__ tag,
                                                            const TX* __restrict__ x, const T* __restrict__ b,
                                                            T* __restrict__ r, Tmpl<T> tp,
-                                                           const T* __restrict__ da = nullptr,
+                                                           int kz, const T* __restrict__ da = nullptr,
                                                            double* __restrict__ part = nullptr, int64_t pt = 0) {
   __shared__ T TC[2][8];
   const int tid = threadIdx.x + kRZX * threadIdx.y;
@@ -1062,7 +1062,7 @@ __global__ void __launch_bounds__(kRZX * kRZY) k_resid_zm3(const uint8_t* __rest
   const int64_t tt = xcd_block(blockIdx.x, gridDim.x);
   const int i = (int)(tt % gbx) * kRZX + threadIdx.x;
   const int j = (int)((tt / gbx) % gby) * kRZY + threadIdx.y;
-  const int z0 = (int)(tt / ((int64_t)gbx * gby)) * kRZ, z1 = min(z0 + kRZ, nz);
+  const int z0 = (int)(tt / ((int64_t)gbx * gby)) * kz, z1 = min(z0 + kz, nz);
   double d0 = 0, d1 = 0;
   if (i < nx && j < ny) {
     const int64_t sxy = (int64_t)nx * ny;
@@ -1252,7 +1252,7 @@ constexpr int kRPX = 128, kRPY = 4, kRPZ = 32;
 template <typename T, int MODE, typename TX = T, int NDOT = 0>
 __global__ void __launch_bounds__(64 * kRPY) k_resid_zp3(const uint8_t* __restrict__ tag,
                                                         const TX* __restrict__ x, const T* __restrict__ b,
-                                                        T* __restrict__ r, Tmpl<T> tp,
+                                                        T* __restrict__ r, Tmpl<T> tp, int kz,
                                                         const T* __restrict__ da = nullptr,
                                                         double* __restrict__ part = nullptr, int64_t pt = 0) {
   typedef TX X2 __attribute__((ext_vector_type(2)));
@@ -1270,7 +1270,7 @@ __global__ void __launch_bounds__(64 * kRPY) k_resid_zp3(const uint8_t* __restri
   const int64_t tt = xcd_block(blockIdx.x, gridDim.x);
   const int i = (int)(tt % gbx) * kRPX + 2 * (int)threadIdx.x;
   const int j = (int)((tt / gbx) % gby) * kRPY + threadIdx.y;
-  const int z0 = (int)(tt / ((int64_t)gbx * gby)) * kRPZ, z1 = min(z0 + kRPZ, nz);
+  const int z0 = (int)(tt / ((int64_t)gbx * gby)) * kz, z1 = min(z0 + kz, nz);
   double d0 = 0, d1 = 0;
   if (i < nx && j < ny) {
     const int64_t sxy = (int64_t)nx * ny;
@@ -1934,18 +1934,19 @@ __global__ void __launch_bounds__(kBlock) k_efield_reg(const uint8_t* __restrict
 }
 
 // The same field of a large 3D level marching along z: each thread owns one
-// (i, j) column of a kEZX x kEZY tile and walks kEZ planes, keeping x of
+// (i, j) column of a kEZX x kEZY tile and walks kz <= kEZ planes, keeping x of
 // planes k - 1, k and k + 1 in registers, so x leaves HBM once (the in-plane
 // neighbours are cache hits) where the plane-by-plane grid re-reads the
 // planes above and below. The arithmetic per component is k_efield_reg's.
 constexpr int kEZX = 64, kEZY = 4, kEZ = 32;
 __global__ void __launch_bounds__(kEZX * kEZY) k_efield_zm3(const uint8_t* __restrict__ tag,
                                                           const double* __restrict__ x, double* __restrict__ E,
-                                                          Tmpl<double> ga, Tmpl<double> gbv, double inv_h) {
+                                                          Tmpl<double> ga, Tmpl<double> gbv, double inv_h,
+                                                          int kz) {
   const int nx = ga.n[0], ny = ga.n[1], nz = ga.n[2];
   const int i = blockIdx.x * kEZX + threadIdx.x;
   const int j = blockIdx.y * kEZY + threadIdx.y;
-  const int z0 = blockIdx.z * kEZ, z1 = min(z0 + kEZ, nz);
+  const int z0 = blockIdx.z * kz, z1 = min(z0 + kz, nz);
   if (i >= nx || j >= ny) return;
   const int64_t sxy = (int64_t)nx * ny, N = sxy * nz;
   int64_t c = i + (int64_t)nx * j + sxy * z0;

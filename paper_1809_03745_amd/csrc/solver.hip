@@ -463,8 +463,23 @@ static void fill(T* x, int64_t n, T v, hipStream_t s) {
 constexpr int64_t kResidZMMin = 1 << 18;
 
 // tiles of the z-marching residual (a 1D grid)
+// Planes a z-marching block walks: most, halved (to at least 4) until the grid
+// has `target` blocks. On a level with few columns a block's walk is the
+// launch's time (a chain of loads per plane) while most of the chip idles:
+// at 64^3 the FP64 residual took 28 us with 32 blocks of 32 planes, and 44 us
+// at 128^3 with 128. The values do not depend on it.
+static int march_planes(int64_t columns, int nz, int most, int64_t target) {
+  int z = most;
+  while (z > 4 && columns * ((nz + z - 1) / z) < target) z /= 2;
+  return z;
+}
+static int64_t zm_cols(const DevLevel& l) {
+  return (int64_t)((l.n[0] + kRZX - 1) / kRZX) * ((l.n[1] + kRZY - 1) / kRZY);
+}
+static int zm_planes(const DevLevel& l) { return march_planes(zm_cols(l), l.n[2], kRZ, 1024); }
 static int64_t zm_resid_blocks(const DevLevel& l) {
-  return (int64_t)((l.n[0] + kRZX - 1) / kRZX) * ((l.n[1] + kRZY - 1) / kRZY) * ((l.n[2] + kRZ - 1) / kRZ);
+  const int z = zm_planes(l);
+  return zm_cols(l) * ((l.n[2] + z - 1) / z);
 }
 
 // blocks of one matrix-vector product on a level (the partials it leaves)
@@ -472,8 +487,13 @@ static int64_t zm_resid_blocks(const DevLevel& l) {
 // kernel (2-element accesses need that, and aligned arrays, which device
 // allocations are)
 static bool pair_ok(const DevLevel& l) { return l.dim == 3 && l.N >= kResidZMMin && l.n[0] % 2 == 0; }
+static int64_t zp_cols(const DevLevel& l) {
+  return (int64_t)((l.n[0] + kRPX - 1) / kRPX) * ((l.n[1] + kRPY - 1) / kRPY);
+}
+static int zp_planes(const DevLevel& l) { return march_planes(zp_cols(l), l.n[2], kRPZ, 1024); }
 static int64_t zp_resid_blocks(const DevLevel& l) {
-  return (int64_t)((l.n[0] + kRPX - 1) / kRPX) * ((l.n[1] + kRPY - 1) / kRPY) * ((l.n[2] + kRPZ - 1) / kRPZ);
+  const int z = zp_planes(l);
+  return zp_cols(l) * ((l.n[2] + z - 1) / z);
 }
 template <typename A>
 static bool al2(const A* p) {
@@ -509,19 +529,25 @@ constexpr int kZMConfigs = 14;   // 7..9: wide-fetch versions of 1, 4, 6 (x exte
                                   // (x extent a multiple of 4)
 static bool zm_cfg_ok(const DevLevel& l, int c) { return (c < 7 || c == 10) || l.n[0] % 4 == 0; }
 
+// blocks a z-marching sweep aims at: two to a CU (at 256^3 32 planes give them,
+// and 16 were slower)
+constexpr int64_t kSweepBlocks = 512;
+
 // zin: x is zero on entry, so the sweep need not read it (not timed by the
 // in-solve hook: it moves fewer bytes than a full sweep)
 template <typename T, int TX, int TY, int KZ, bool WIDE = false>
 static void launch_zm_cfg(DevLevel& l, const T* xin, T* xout, const T* b, const Tmpl<T>& tp, hipStream_t s,
                           bool zin) {
   if (WIDE && l.n[0] % 4 != 0) throw ArgError("the wide-fetch sweep needs an x extent that is a multiple of 4");
-  const int64_t nb = (int64_t)((l.n[0] + TX - 1) / TX) * ((l.n[1] + TY - 1) / TY) * ((l.n[2] + KZ - 1) / KZ);
+  const int64_t nc = (int64_t)((l.n[0] + TX - 1) / TX) * ((l.n[1] + TY - 1) / TY);
+  const int kz = march_planes(nc, l.n[2], KZ, kSweepBlocks);
+  const int64_t nb = nc * ((l.n[2] + kz - 1) / kz);
   if (zin)
     hipLaunchKernelGGL((k_rb_zm3<T, TX, TY, KZ, WIDE, true>), dim3((unsigned)nb), dim3(TX * TY / 2), 0, s, l.tag.p,
-                       xin, xout, b, tp, l.N2);
+                       xin, xout, b, tp, l.N2, kz);
   else
     KLAUNCH(l.kt, (k_rb_zm3<T, TX, TY, KZ, WIDE>), dim3((unsigned)nb), dim3(TX * TY / 2), 0, s, l.tag.p, xin, xout,
-            b, tp, l.N2);
+            b, tp, l.N2, kz);
 }
 
 template <typename T, int TX, int TY, int KZ, int OCC>
@@ -536,13 +562,15 @@ static void launch_zq_cfg(DevLevel& l, const T* xin, T* xout, const T* b, const 
     launch_zm_cfg<T, 64, 16, 32>(l, xin, xout, b, tp, s, zin);
     return;
   }
-  const int64_t nb = (int64_t)((l.n[0] + TX - 1) / TX) * ((l.n[1] + TY - 1) / TY) * ((l.n[2] + KZ - 1) / KZ);
+  const int64_t nc = (int64_t)((l.n[0] + TX - 1) / TX) * ((l.n[1] + TY - 1) / TY);
+  const int kz = march_planes(nc, l.n[2], KZ, kSweepBlocks);
+  const int64_t nb = nc * ((l.n[2] + kz - 1) / kz);
   if (zin)
     hipLaunchKernelGGL((k_rb_zq3<T, TX, TY, KZ, OCC, true>), dim3((unsigned)nb), dim3(TX * TY / 4), 0, s, l.tag.p, xin,
-                       xout, b, tp, l.N2);
+                       xout, b, tp, l.N2, kz);
   else
     KLAUNCH(l.kt, (k_rb_zq3<T, TX, TY, KZ, OCC>), dim3((unsigned)nb), dim3(TX * TY / 4), 0, s, l.tag.p, xin, xout, b,
-            tp, l.N2);
+            tp, l.N2, kz);
 }
 
 template <typename T>
@@ -1478,10 +1506,10 @@ static void residual(DevLevel& l, const T* x, const T* b, T* r, hipStream_t s) {
     KTiming* kr = (sizeof(T) == 8 && MODE == 0) ? l.ktr : nullptr;
     if (sizeof(T) == 8 && pair_ok(l) && al2(x) && al2(b) && al2(r))
       KLAUNCH(kr, (k_resid_zp3<T, MODE>), dim3((unsigned)zp_resid_blocks(l)), dim3(64, kRPY), 0, s, l.tag.p, x, b, r,
-              tp, (const T*)nullptr, (double*)nullptr, (int64_t)0);
+              tp, zp_planes(l), (const T*)nullptr, (double*)nullptr, (int64_t)0);
     else
       KLAUNCH(kr, (k_resid_zm3<T, MODE>), dim3((unsigned)zm_resid_blocks(l)), dim3(kRZX, kRZY), 0, s, l.tag.p, x, b,
-              r, tp, (const T*)nullptr, (double*)nullptr, (int64_t)0);
+              r, tp, zm_planes(l), (const T*)nullptr, (double*)nullptr, (int64_t)0);
     residual_rows<T, MODE>(l, x, b, r, s);
   } else {
     // small levels: template cells and explicit rows in one launch
@@ -1506,10 +1534,10 @@ static void apply_split(DevLevel& l, const double* x, const double* x2, double* 
   if (l.dim == 3 && l.N >= kResidZMMin) {
     if (pair_ok(l) && al2(x) && al2(out))
       hipLaunchKernelGGL((k_resid_zp3<double, 1>), dim3((unsigned)zp_resid_blocks(l)), dim3(64, kRPY), 0, s, l.tag.p, x,
-                         none, out, tp, none, (double*)nullptr, (int64_t)0);
+                         none, out, tp, zp_planes(l), none, (double*)nullptr, (int64_t)0);
     else
       hipLaunchKernelGGL((k_resid_zm3<double, 1>), dim3((unsigned)zm_resid_blocks(l)), dim3(kRZX, kRZY), 0, s, l.tag.p,
-                         x, none, out, tp, none, (double*)nullptr, (int64_t)0);
+                         x, none, out, tp, zm_planes(l), none, (double*)nullptr, (int64_t)0);
     if (l.R > 0) {
       const BLev<double> L = make_blev<double>(l);
       const int nb0 = (L.grp_ptr[1] - L.grp_ptr[0] + kSplitRows - 1) / kSplitRows;
@@ -1852,12 +1880,12 @@ static void efield(ebmg_problem_s* P, const double* x, const double* x2, const d
     }
   const double ih = 1.0 / H.levels[0].g.h;
   const Shape sh = shape3(L.n[0], L.n[1], L.dim == 3 ? L.n[2] : 1);
-  if (L.dim == 3 && L.N >= kResidZMMin)
-    hipLaunchKernelGGL(k_efield_zm3,
-                       dim3((unsigned)((L.n[0] + kEZX - 1) / kEZX), (unsigned)((L.n[1] + kEZY - 1) / kEZY),
-                            (unsigned)((L.n[2] + kEZ - 1) / kEZ)),
-                       dim3(kEZX, kEZY), 0, s, L.tag.p, x, E, ga, gb, ih);
-  else if (L.dim == 3)
+  if (L.dim == 3 && L.N >= kResidZMMin) {
+    const unsigned cx = (unsigned)((L.n[0] + kEZX - 1) / kEZX), cy = (unsigned)((L.n[1] + kEZY - 1) / kEZY);
+    const int kz = march_planes((int64_t)cx * cy, L.n[2], kEZ, 1024);
+    hipLaunchKernelGGL(k_efield_zm3, dim3(cx, cy, (unsigned)((L.n[2] + kz - 1) / kz)), dim3(kEZX, kEZY), 0, s, L.tag.p,
+                       x, E, ga, gb, ih, kz);
+  } else if (L.dim == 3)
     hipLaunchKernelGGL((k_efield_reg<3>), sh.g, sh.b, 0, s, L.tag.p, x, E, ga, gb, ih);
   else
     hipLaunchKernelGGL((k_efield_reg<2>), sh.g, sh.b, 0, s, L.tag.p, x, E, ga, gb, ih);
@@ -1883,6 +1911,7 @@ static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da
   if (l.dim == 3 && l.N >= kResidZMMin) {
     const bool pair = pair_ok(l) && al2(x) && al2(out) && al2(da);
     const dim3 g((unsigned)(pair ? zp_resid_blocks(l) : zm_resid_blocks(l)));
+    const int kz = pair ? zp_planes(l) : zm_planes(l);
     const int64_t G = (int64_t)g.x;
     // explicit rows: the sliced copy (one thread per row) where there is one
     const bool sl = l.R > 0 && l.sl_ptr.p;
@@ -1897,16 +1926,16 @@ static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da
     if ((int64_t)ndot * pt > D.part.n) throw DeviceError("matrix-vector partials exceed their buffer");
     if (pair) {
       if (ndot == 1)
-        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 1>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, da,
+        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 1>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
                            D.part.p, pt);
       else
-        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 2>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, da,
+        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 2>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
                            D.part.p, pt);
     } else if (ndot == 1) {
-      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 1>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, da,
+      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 1>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
                          D.part.p, pt);
     } else {
-      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 2>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, da,
+      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 2>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
                          D.part.p, pt);
     }
     if (sl) {
@@ -3655,11 +3684,11 @@ ebmg_status ebmg_time_kernel(ebmg_problem pb, int32_t which, int32_t level, int3
       } else {
         if (pair_ok(L)) {
           hipLaunchKernelGGL((k_resid_zp3<double, 0>), dim3((unsigned)zp_resid_blocks(L)), dim3(64, kRPY), 0, s,
-                             L.tag.p, L.x64.p, L.b64.p, L.r64.p, L.t64);
+                             L.tag.p, L.x64.p, L.b64.p, L.r64.p, L.t64, zp_planes(L));
         } else if (L.dim == 3 && L.N >= kResidZMMin) {
           const dim3 g((unsigned)zm_resid_blocks(L));
           hipLaunchKernelGGL((k_resid_zm3<double, 0>), g, dim3(kRZX, kRZY), 0, s, L.tag.p, L.x64.p, L.b64.p,
-                             L.r64.p, L.t64);
+                             L.r64.p, L.t64, zm_planes(L));
         } else if (L.dim == 3) {
           hipLaunchKernelGGL((k_resid_reg<double, 3, 0>), shf.g, shf.b, 0, s, L.tag.p, L.x64.p, L.b64.p, L.r64.p, L.t64);
         } else {

@@ -88,7 +88,8 @@ __device__ __forceinline__ void zq_ring_cell(int i, int& c, int& r) {
 template <typename T, int TX, int TY, int KZ, int OCC, bool ZIN = false>
 __global__ void __launch_bounds__(TX * TY / 4, OCC) k_rb_zq3(const uint8_t* __restrict__ tag,
                                                          const T* __restrict__ xin, T* __restrict__ xout,
-                                                         const T* __restrict__ b, Tmpl<T> tp, int64_t nsec) {
+                                                         const T* __restrict__ b, Tmpl<T> tp, int64_t nsec,
+                                                                        int kz) {
   typedef T Q __attribute__((ext_vector_type(4)));
   constexpr int NT = TX * TY / 4, QX = TX / 4, RPW = 64 / QX;
   constexpr int PQ = QX + 2, PW = 4 * PQ, PH = TY + 4, NQ = PQ * PH;   // LDS plane: columns -4 .. TX+3, rows -2 .. TY+1
@@ -104,8 +105,8 @@ __global__ void __launch_bounds__(TX * TY / 4, OCC) k_rb_zq3(const uint8_t* __re
   const int64_t nblocks = (int64_t)gridDim.x;
   const int64_t t = xcd_block(blockIdx.x, nblocks);
   const int x0 = (int)(t % bx) * TX, y0 = (int)((t / bx) % by) * TY;
-  const int z0 = (int)(t / ((int64_t)bx * by)) * KZ;
-  const int z1 = min(z0 + KZ, nz);
+  const int z0 = (int)(t / ((int64_t)bx * by)) * kz;   // kz: KZ, or fewer on small levels
+  const int z1 = min(z0 + kz, nz);
   const int tid = threadIdx.x;
   const int64_t sxy = (int64_t)nx * ny;
   if (tid < 16) {
