@@ -31,6 +31,7 @@
 #include "batch_wide.hpp"
 #include "kernels.hpp"
 #include "zq_kernels.hpp"
+#include "tile_kernels.hpp"
 #include "sdf_kernels.hpp"
 #include "adv_kernels.hpp"
 #include "amr_kernels.hpp"
@@ -141,6 +142,27 @@ struct KTiming {
     }                                                                                                 \
   } while (0)
 
+// A small level's tiles (see tile_kernels.hpp): what each tile reads of the
+// explicit rows and transfer lists. Values and diagonals stay the level's.
+struct DevTiles {
+  int halo = 0;              // 0: not tiled
+  int nt[3] = {1, 1, 1};
+  DevBuf<int32_t> ptr, rid, npp, npc, nsp, nsd, nsq;
+  DevBuf<TileRow> row;
+  DevBuf<uint16_t> lcol, npl, nsl;
+  int64_t share(const DevTiles& o) {
+    halo = o.halo;
+    for (int d = 0; d < 3; ++d) nt[d] = o.nt[d];
+    return ptr.share(o.ptr) + rid.share(o.rid) + npp.share(o.npp) + npc.share(o.npc) + nsp.share(o.nsp) +
+           nsd.share(o.nsd) + nsq.share(o.nsq) + row.share(o.row) + lcol.share(o.lcol) + npl.share(o.npl) +
+           nsl.share(o.nsl);
+  }
+  void release() {
+    ptr.release(); rid.release(); npp.release(); npc.release(); nsp.release(); nsd.release(); nsq.release();
+    row.release(); lcol.release(); npl.release(); nsl.release();
+  }
+};
+
 struct DevLevel {
   int dim = 2;
   int n[3] = {1, 1, 1};
@@ -163,6 +185,7 @@ struct DevLevel {
   bool oop = false;                // non-fused: one-launch colour phases (else split in place)
   int fvar = 0;                    // fused variant: 0 3D/2D tile, 1 z-marching (3D)
   int zmcfg = 0;                   // z-marching tile configuration
+  DevTiles tiles;                  // one launch per V-cycle side (small levels)
   KTiming* kt = nullptr;           // sweep launches timed during solves (or none)
   KTiming* ktr = nullptr;          // FP64 residual launches timed during solves (or none)
   double tune_split_ms = 0, tune_fused_ms = 0, tune_zm_ms = 0, tune_oop_ms = 0;
@@ -179,6 +202,7 @@ struct DevLevel {
     sl_ptr.release(); sl_col.release(); sl_colj.release(); sl_val64.release(); sl_val32.release();
     x64.release(); b64.release(); r64.release(); x32.release(); b32.release(); r32.release();
     w64.release(); w32.release(); xa64.release(); xa32.release();
+    tiles.release();
   }
 };
 
@@ -1120,6 +1144,135 @@ static bool recoefficientable(const Problem& H) {
   return H.geo.obj_value.empty() && H.geo.N2 == 0 && H.levels[0].irow_dof.empty();
 }
 
+// Levels of at most this many cells take the one-launch V-cycle sides.
+// Measured per V-cycle side against the launches it replaces (FP64, two
+// sweeps): 2D 1024^2 with rows of reach 3 26 us against 60, 512^2 (reach 2)
+// 14 against 45, 256^2 and below 9 to 11 against 21; 3D 64^3 18 against 27,
+// 32^3 and 16^3 9 to 10 against 21 (12 to 18 with many rows). At 128^3 the
+// eightfold cell work would cost about 130 us against 60; 2D levels above
+// 1024^2 were not measured and keep their sweeps.
+constexpr int64_t kTileMax2 = 1 << 20, kTileMax3 = 1 << 18;
+
+// The tiles of level L (rows in device order, C the next coarser level), or
+// none where a launch could not advance its four phases in a tile's halo: a
+// row that reads beyond its neighbouring cells, or more rows than a tile holds.
+template <int DIM, int H>
+static void upload_tiles(DevLevel& d, const Level& L, const Level& C, const DevRows& rows, hipStream_t s,
+                         int64_t& by) {
+  using TD = TileDim<DIM, H>;
+  const int E = TD::E, W = TD::C;
+  DevTiles& t = d.tiles;
+  int nt[3] = {1, 1, 1};
+  for (int e = 0; e < DIM; ++e) nt[e] = (L.g.n[e] + W - 1) / W;
+  const int ntile = nt[0] * nt[1] * nt[2];
+  const int64_t nx = L.g.n[0], ny = L.g.n[1];
+  struct At { int v[3]; };
+  auto at = [&](int64_t c) { return At{{(int)(c % nx), (int)(c / nx % ny), (int)(c / nx / ny)}}; };
+  auto cell = [&](int64_t q) { return q < L.N ? q : (int64_t)L.sec_cell[q - L.N]; };
+  auto place = [&](int tile, const At& a, bool& core) {   // in the tile's cells, or -1
+    const int o[3] = {tile % nt[0] * W, tile / nt[0] % nt[1] * W, tile / nt[0] / nt[1] * W};
+    int m = 0;
+    core = true;
+    for (int e = DIM - 1; e >= 0; --e) {
+      const int l = a.v[e] - o[e] + H;
+      if (l < 0 || l >= E) return -1;
+      core = core && l >= H && l < E - H;
+      m = m * E + l;
+    }
+    return m;
+  };
+  // f(tile) for the tiles that hold cell a, halo included
+  auto each = [&](const At& a, auto&& f) {
+    int lo[3] = {0, 0, 0}, hi[3] = {0, 0, 0};
+    for (int e = 0; e < DIM; ++e) {
+      lo[e] = a.v[e] < H ? 0 : (a.v[e] - H) / W;
+      hi[e] = std::min(nt[e] - 1, (a.v[e] + H) / W);
+    }
+    for (int k = lo[2]; k <= hi[2]; ++k)
+      for (int j = lo[1]; j <= hi[1]; ++j)
+        for (int i = lo[0]; i <= hi[0]; ++i) f(i + nt[0] * (j + nt[1] * k));
+  };
+  const int64_t R = (int64_t)rows.dof.size();
+  const std::vector<int32_t> gptr = group_ptr(L);
+  std::vector<std::vector<int32_t>> list(ntile), npt(ntile), nst(ntile);
+  for (int64_t r = 0; r < R; ++r) {
+    const At a = at(cell(rows.dof[r]));
+    for (int64_t e = rows.rp[r]; e < rows.rp[r + 1]; ++e) {
+      const At c = at(cell(rows.col[e]));
+      for (int x = 0; x < DIM; ++x)
+        if (std::abs(c.v[x] - a.v[x]) * kTilePhases > H) return;
+    }
+    each(a, [&](int tile) { list[tile].push_back((int32_t)r); });
+  }
+  for (const auto& l : list)
+    if ((int)l.size() > kTileRows) return;
+  for (size_t q = 0; q < L.np_fdof.size(); ++q)
+    each(at(cell(L.np_fdof[q])), [&](int tile) { npt[tile].push_back((int32_t)q); });
+  for (size_t q = 0; q < L.ns_cdof.size(); ++q) {
+    const int64_t P = L.ns_cdof[q] < C.N ? L.ns_cdof[q] : (int64_t)C.sec_cell[L.ns_cdof[q] - C.N];
+    const int64_t cx = C.g.n[0], cy = C.g.n[1];
+    const int I[3] = {(int)(P % cx), (int)(P / cx % cy), (int)(P / cx / cy)};
+    nst[I[0] / (W / 2) + nt[0] * (I[1] / (W / 2) + nt[1] * (DIM == 3 ? I[2] / (W / 2) : 0))].push_back((int32_t)q);
+  }
+  std::vector<int32_t> ptr{0}, rid, npp{0}, npc, nsp{0}, nsd, nsq{0};
+  std::vector<TileRow> row;
+  std::vector<uint16_t> lcol, npl, nsl;
+  std::vector<int32_t> slot(L.N2, 0), seen(L.N2, -1);   // place of a second-phase unknown's row in the tile's list
+  for (int tile = 0; tile < ntile; ++tile) {
+    const auto& l = list[tile];
+    for (size_t k = 0; k < l.size(); ++k)
+      if (rows.dof[l[k]] >= L.N) {
+        slot[rows.dof[l[k]] - L.N] = (int32_t)k;
+        seen[rows.dof[l[k]] - L.N] = tile;
+      }
+    bool core = false;
+    auto loc = [&](int64_t q) -> int {   // an unknown's place in the tile's LDS, or -1
+      const int m = place(tile, at(cell(q)), core);
+      if (m < 0 || q < L.N) return m;
+      return seen[q - L.N] == tile ? TD::NE + slot[q - L.N] : -1;
+    };
+    int g1 = 0;
+    for (int32_t r : l) {
+      if (r < gptr[1]) ++g1;
+      TileRow w;
+      w.beg = (int32_t)rows.rp[r];
+      w.lcol = (int32_t)lcol.size();
+      w.dof = (int32_t)rows.dof[r];
+      const int m = loc(rows.dof[r]);
+      if (m < 0) throw std::runtime_error("explicit row outside its tile");
+      w.bits = (uint32_t)m | (uint32_t)(rows.rp[r + 1] - rows.rp[r]) << 13 | (core ? 1u << 31 : 0u);
+      row.push_back(w);
+      rid.push_back(r);
+      for (int64_t e = rows.rp[r]; e < rows.rp[r + 1]; ++e) lcol.push_back((uint16_t)std::max(0, loc(rows.col[e])));
+    }
+    ptr.push_back(ptr.back() + g1);
+    ptr.push_back((int32_t)row.size());
+    for (int32_t q : npt[tile]) {
+      const int m = loc(L.np_fdof[q]);
+      if (m < 0) return;   // a second-phase unknown without a row
+      npl.push_back((uint16_t)m);
+      npc.push_back((int32_t)L.np_cdof[q]);
+    }
+    npp.push_back((int32_t)npc.size());
+    for (int32_t q : nst[tile]) {
+      nsd.push_back((int32_t)L.ns_cdof[q]);
+      for (int32_t e = L.ns_ptr[q]; e < L.ns_ptr[q + 1]; ++e) {
+        const int m = loc(L.ns_child[e]);
+        if (m < 0) return;
+        nsl.push_back((uint16_t)m);
+      }
+      nsq.push_back((int32_t)nsl.size());
+    }
+    nsp.push_back((int32_t)nsd.size());
+  }
+  auto put = [&](auto& b, const auto& v) { b.upload(v.data(), (int64_t)v.size(), s, by); };
+  put(t.ptr, ptr); put(t.rid, rid); put(t.npp, npp); put(t.npc, npc); put(t.nsp, nsp); put(t.nsd, nsd);
+  put(t.nsq, nsq); put(t.row, row); put(t.lcol, lcol); put(t.npl, npl); put(t.nsl, nsl);
+  HIPCHECK(hipStreamSynchronize(s));
+  for (int e = 0; e < 3; ++e) t.nt[e] = nt[e];
+  t.halo = H;
+}
+
 // Upload a problem's hierarchy. With `share` (a family member set up on the
 // same geometry as `share`), every level whose structure equals share's
 // takes share's device structure arrays instead of its own copies (the
@@ -1225,6 +1378,19 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
     }
     d.t64 = make_tmpl<double>(L);
     d.t32 = make_tmpl<float>(L);
+    if (sd) {
+      D.shared_bytes += d.tiles.share(sd->tiles);
+    } else if (!batch_box && l + 1 < H.levels.size() && (H.opt.smoother == 0 || H.opt.smoother == 4) &&
+               L.N <= (L.g.dim == 3 ? kTileMax3 : kTileMax2)) {
+      const Level& C = H.levels[l + 1];
+      if (L.g.dim == 3) {
+        upload_tiles<3, 4>(d, L, C, rows, s, by);
+      } else {
+        upload_tiles<2, 4>(d, L, C, rows, s, by);
+        if (!d.tiles.halo) upload_tiles<2, 8>(d, L, C, rows, s, by);
+        if (!d.tiles.halo) upload_tiles<2, 12>(d, L, C, rows, s, by);
+      }
+    }
     const int64_t nd = L.N + L.N2;
     // the work array holds the explicit rows' Jacobi values and, after them,
     // group 1's values before its pass (k_irr_jac_sl0c)
@@ -1659,8 +1825,69 @@ static void prolong_from(DevLevel& f, DevLevel& c, const T* ec, T* xf, hipStream
 }
 
 
+// Whether level l of a V-cycle from zero runs each side in one launch: its
+// tiles exist, the halo holds the sweeps, and no level-0 launch is timed.
+static bool tiled(const DevProblem& D, const Options& o, size_t l) {
+  const DevLevel& L = D.lv[l];
+  return L.tiles.halo > 0 && 2 * std::max(o.nu1, o.nu2) <= kTilePhases && !L.kt && (int)l != D.tail_l0;
+}
+
+// Whether a V-cycle told that its x is zero never reads it on level 0 (x need
+// not be cleared then).
 template <typename T>
-// xz: x holds zeros on entry (lets the first z-marching sweep skip reading it)
+static bool zero_start(DevProblem& D, const Options& o) {
+  DevLevel& L = D.lv[0];
+  return Vec<T>::xa(L) && D.lv.size() > 1 && D.tail_l0 != 0 &&
+         (tiled(D, o, 0) || (L.dim == 3 && L.fused && L.fvar == 1 && o.nu1 > 0));
+}
+
+template <typename T, bool PRE>
+static void launch_tile(DevLevel& l, DevLevel& c, const T* xin, const T* ec, const T* b, T* xo, T* bc, int sweeps,
+                        hipStream_t s) {
+  const DevTiles& t = l.tiles;
+  TileView<T> v;
+  v.tp = Vec<T>::t(l);
+  for (int e = 0; e < 3; ++e) {
+    v.cn[e] = c.n[e];
+    v.nt[e] = t.nt[e];
+  }
+  v.tag = l.tag.p;
+  v.ctag = c.tag.p;
+  v.val = Vec<T>::val(l);
+  v.diag = Vec<T>::diag(l);
+  v.ptr = t.ptr.p;
+  v.row = t.row.p;
+  v.rid = t.rid.p;
+  v.lcol = t.lcol.p;
+  v.npp = t.npp.p;
+  v.npl = t.npl.p;
+  v.npc = t.npc.p;
+  v.nsp = t.nsp.p;
+  v.nsd = t.nsd.p;
+  v.nsq = t.nsq.p;
+  v.nsl = t.nsl.p;
+  const dim3 g((unsigned)(t.nt[0] * t.nt[1] * t.nt[2]));
+  const bool rows = l.R > 0 || l.n_ns > 0 || l.n_np > 0;
+#define TILE_LAUNCH(DIM, H, ROWS)                                                                             \
+  hipLaunchKernelGGL((k_tile<T, DIM, H, PRE, ROWS>), g, dim3(TileDim<DIM, H>::NT), 0, s, v, xin, ec, b, xo, bc, \
+                     2 * sweeps)
+  if (l.dim == 3) {
+    if (rows) TILE_LAUNCH(3, 4, true); else TILE_LAUNCH(3, 4, false);
+  } else if (t.halo == 4) {
+    if (rows) TILE_LAUNCH(2, 4, true); else TILE_LAUNCH(2, 4, false);
+  } else if (t.halo == 8) {
+    TILE_LAUNCH(2, 8, true);
+  } else {
+    TILE_LAUNCH(2, 12, true);
+  }
+#undef TILE_LAUNCH
+  HIPCHECK(hipGetLastError());
+}
+
+template <typename T>
+// xz: x is to be taken as zeros on entry (levels below the first one always;
+// it is not read where the level is tiled or its first sweep is the
+// z-marching one, and holds zeros elsewhere)
 static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz) {
   DevLevel& L = D.lv[l];
   if ((int)l == D.tail_l0) {
@@ -1691,6 +1918,15 @@ static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* 
     return;
   }
   DevLevel& C = D.lv[l + 1];
+  if (xz && tiled(D, o, l) && Vec<T>::xa(L)) {
+    T* xa = Vec<T>::xa(L);
+    launch_tile<T, true>(L, C, nullptr, nullptr, b, xa, Vec<T>::b(C), o.nu1, s);
+    // the bottom solves and tiled levels write their x without reading it
+    if (l + 2 < D.lv.size() && !tiled(D, o, l + 1)) fill<T>(Vec<T>::x(C), C.N + C.N2, T(0), s);
+    vcycle<T>(D, o, l + 1, s, Vec<T>::x(C), Vec<T>::b(C), true);
+    launch_tile<T, false>(L, C, xa, Vec<T>::x(C), b, x, nullptr, o.nu2, s);
+    return;
+  }
   smooth<T>(L, x, b, o.nu1, s, xz);
   residual_restrict<T>(L, C, x, b, s);   // also clears the coarse x
   vcycle<T>(D, o, l + 1, s, Vec<T>::x(C), Vec<T>::b(C), true);
@@ -1705,12 +1941,14 @@ static void precond(DevProblem& D, const Options& o, const double* r, double* z,
   const int64_t nd = L.N + L.N2;
   if (o.precision == EBMG_MIXED) {
     hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(nd)), dim3(kBlock), 0, s, r, L.b32.p, nd);
-    fill<float>(L.x32.p, nd, 0.0f, s);
-    vcycle<float>(D, o, 0, s, L.x32.p, L.b32.p);
+    const bool zin = zero_start<float>(D, o);
+    if (!zin) fill<float>(L.x32.p, nd, 0.0f, s);
+    vcycle<float>(D, o, 0, s, L.x32.p, L.b32.p, zin);
     hipLaunchKernelGGL((k_convert<float, double>), dim3(nblk(nd)), dim3(kBlock), 0, s, L.x32.p, z, nd);
   } else {
-    fill<double>(z, nd, 0.0, s);
-    vcycle<double>(D, o, 0, s, z, r);
+    const bool zin = zero_start<double>(D, o);
+    if (!zin) fill<double>(z, nd, 0.0, s);
+    vcycle<double>(D, o, 0, s, z, r, zin);
   }
   HIPCHECK(hipGetLastError());
 }
@@ -2003,8 +2241,8 @@ static ebmg_status bicgstab_t(DevProblem& D, const Options& o, double bn, double
   };
   // the preconditioner output starts from zero: cleared by the p- and
   // s-updates, unless the finest level's first sweep is the z-marching one,
-  // which then takes x = 0 without reading it
-  const bool zin = L.dim == 3 && L.fused && L.fvar == 1 && Vec<Z>::xa(L) && D.tail_l0 != 0 && o.nu1 > 0;
+  // which then takes x = 0 without reading it, or the level is tiled
+  const bool zin = zero_start<Z>(D, o);
   auto vcyc = [&](Z* z, const double* in, hipStream_t q) {
     if constexpr (std::is_same<Z, float>::value) {
       (void)in;
@@ -2127,8 +2365,9 @@ static ebmg_status solve(ebmg_problem_s* P, const double* rho, const double* sig
       auto cycle = [&](hipStream_t q) {
         if (mixed) {
           hipLaunchKernelGGL((k_convert<double, float>), dim3(nblk(nd)), dim3(kBlock), 0, q, L.r64.p, L.b32.p, nd);
-          fill<float>(L.x32.p, nd, 0.0f, q);
-          vcycle<float>(D, H.opt, 0, q, L.x32.p, L.b32.p);
+          const bool zin = zero_start<float>(D, H.opt);
+          if (!zin) fill<float>(L.x32.p, nd, 0.0f, q);
+          vcycle<float>(D, H.opt, 0, q, L.x32.p, L.b32.p, zin);
           hipLaunchKernelGGL(k_add_f32, dim3(nblk(nd)), dim3(kBlock), 0, q, L.x64.p, L.x32.p, nd);
         } else {
           vcycle<double>(D, H.opt, 0, q, L.x64.p, L.b64.p);
