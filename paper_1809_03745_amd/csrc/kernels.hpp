@@ -1604,6 +1604,11 @@ __global__ void __launch_bounds__(64) k_bottom(const double* __restrict__ Ainv, 
   if (lane == 0) x[row] = (T)s;
 }
 
+// BiCGStab scalars live on the device: slots of `sc`
+// SC_GUESS: 1 when the initial guess has a nonzero entry (set by k_guess_in);
+// SC_FIRST: 1 from a (re)start until the first iteration's omega step
+enum { SC_RHO = 0, SC_RR, SC_RHO_OLD, SC_ALPHA, SC_OMEGA, SC_RV, SC_TS, SC_TT, SC_GUESS, SC_FIRST, SC_NUM };
+
 // Deterministic dot products: a fixed grid of per-block partials (wave64
 // shuffles, then a fixed-order sum of the block's waves), then one block sums
 // the partials in a fixed order. No atomics, so results are bitwise
@@ -1637,8 +1642,15 @@ __global__ void __launch_bounds__(kBlock) k_dot_partial(const T* __restrict__ a,
 }
 
 // sums `nvec` consecutive partial arrays of length n into out[0..nvec)
+// The last launch before the host looks at the scalars also does what used to
+// follow in launches of one thread (op: BiCGStab's alpha or omega from the new
+// sums) and writes the nsc scalars at sc into host memory, then a 1 behind
+// them: a copy launched for it cost 8 us to start and 4 to run, and the host
+// sees the 1 before a stream synchronisation would return.
+enum { DOT_ONLY = 0, DOT_ALPHA, DOT_OMEGA };
 __global__ void __launch_bounds__(kBlock) k_dot_final(const double* __restrict__ part, int n, int nvec,
-                                                      double* __restrict__ out) {
+                                                      double* out, int op = DOT_ONLY, double* sc = nullptr,
+                                                      int nsc = 0, double* host = nullptr) {
   // nvec is 1 or 2; both sums are formed together, four strided terms per
   // step with their loads issued first, each sum taking its terms in the
   // order of the plain strided loop and then the fixed wave/block order
@@ -1687,13 +1699,19 @@ __global__ void __launch_bounds__(kBlock) k_dot_final(const double* __restrict__
     }
     out[0] = tot0;
     if (two) out[1] = tot1;
+    if (op == DOT_ALPHA) sc[SC_ALPHA] = sc[SC_RHO] / sc[SC_RV];
+    if (op == DOT_OMEGA) {
+      sc[SC_OMEGA] = sc[SC_TT] > 0.0 ? sc[SC_TS] / sc[SC_TT] : 0.0;
+      sc[SC_RHO_OLD] = sc[SC_RHO];
+      sc[SC_FIRST] = 0.0;
+    }
+    if (host) {
+      for (int q = 0; q < nsc; ++q) host[q] = sc[q];
+      __threadfence_system();
+      *(volatile double*)(host + nsc) = 1.0;
+    }
   }
 }
-
-// BiCGStab scalars live on the device: slots of `sc`
-// SC_GUESS: 1 when the initial guess has a nonzero entry (set by k_guess_in);
-// SC_FIRST: 1 from a (re)start until the first iteration's omega step
-enum { SC_RHO = 0, SC_RR, SC_RHO_OLD, SC_ALPHA, SC_OMEGA, SC_RV, SC_TS, SC_TT, SC_GUESS, SC_FIRST, SC_NUM };
 
 __global__ void k_sc_reset(double* sc) {
   sc[SC_RHO] = 1.0;
@@ -1704,14 +1722,6 @@ __global__ void k_sc_reset(double* sc) {
 }
 
 __global__ void k_sc_copy(double* sc, int dst, int src) { sc[dst] = sc[src]; }
-
-__global__ void k_sc_alpha(double* sc) { sc[SC_ALPHA] = sc[SC_RHO] / sc[SC_RV]; }
-
-__global__ void k_sc_omega(double* sc) {
-  sc[SC_OMEGA] = sc[SC_TT] > 0.0 ? sc[SC_TS] / sc[SC_TT] : 0.0;
-  sc[SC_RHO_OLD] = sc[SC_RHO];
-  sc[SC_FIRST] = 0.0;
-}
 
 // Fused BiCGStab vector steps. p = r + beta (p - omega v) (resp. s = r -
 // alpha v) also clears the preconditioner output z and, for mixed precision,

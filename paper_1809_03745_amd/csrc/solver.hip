@@ -674,7 +674,8 @@ static BLev<T> make_blev(DevLevel& l) {
 }
 
 template <typename T>
-static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz = false);
+static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz = false,
+                   bool add = false);
 
 // Tail autotuner: time a whole V-cycle (on zero vectors) with the one-
 // workgroup engine starting at each level of at most kTailMax unknowns, and
@@ -1459,7 +1460,7 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
   D.objv.alloc(std::max<int64_t>(1, (int64_t)H.geo.obj_value.size()), by);
   D.part.alloc(std::max<int64_t>(2 * kNormBlocks, 2 * matvec_blocks(D.lv[0])), by);
   D.scal.alloc(SC_NUM, by);
-  HIPCHECK(hipHostMalloc((void**)&D.host_scal, SC_NUM * sizeof(double), hipHostMallocDefault));
+  HIPCHECK(hipHostMalloc((void**)&D.host_scal, (SC_NUM + 1) * sizeof(double), hipHostMallocCoherent));
   D.krylov = H.opt.krylov == 2;
   if (batch_box) {
     // the in-group solver keeps its Krylov / correction vectors here
@@ -1843,7 +1844,7 @@ static bool zero_start(DevProblem& D, const Options& o) {
 
 template <typename T, bool PRE>
 static void launch_tile(DevLevel& l, DevLevel& c, const T* xin, const T* ec, const T* b, T* xo, T* bc, int sweeps,
-                        hipStream_t s) {
+                        hipStream_t s, bool add = false) {
   const DevTiles& t = l.tiles;
   TileView<T> v;
   v.tp = Vec<T>::t(l);
@@ -1870,7 +1871,7 @@ static void launch_tile(DevLevel& l, DevLevel& c, const T* xin, const T* ec, con
   const bool rows = l.R > 0 || l.n_ns > 0 || l.n_np > 0;
 #define TILE_LAUNCH(DIM, H, ROWS)                                                                             \
   hipLaunchKernelGGL((k_tile<T, DIM, H, PRE, ROWS>), g, dim3(TileDim<DIM, H>::NT), 0, s, v, xin, ec, b, xo, bc, \
-                     2 * sweeps)
+                     2 * sweeps, add)
   if (l.dim == 3) {
     if (rows) TILE_LAUNCH(3, 4, true); else TILE_LAUNCH(3, 4, false);
   } else if (t.halo == 4) {
@@ -1887,8 +1888,9 @@ static void launch_tile(DevLevel& l, DevLevel& c, const T* xin, const T* ec, con
 template <typename T>
 // xz: x is to be taken as zeros on entry (levels below the first one always;
 // it is not read where the level is tiled or its first sweep is the
-// z-marching one, and holds zeros elsewhere)
-static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz) {
+// z-marching one, and holds zeros elsewhere); add (a tiled level, xz): the
+// result is added to x instead
+static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz, bool add) {
   DevLevel& L = D.lv[l];
   if ((int)l == D.tail_l0) {
     const BLev<T>* lv = (const BLev<T>*)D.tail_lv.p;
@@ -1924,7 +1926,7 @@ static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* 
     // the bottom solves and tiled levels write their x without reading it
     if (l + 2 < D.lv.size() && !tiled(D, o, l + 1)) fill<T>(Vec<T>::x(C), C.N + C.N2, T(0), s);
     vcycle<T>(D, o, l + 1, s, Vec<T>::x(C), Vec<T>::b(C), true);
-    launch_tile<T, false>(L, C, xa, Vec<T>::x(C), b, x, nullptr, o.nu2, s);
+    launch_tile<T, false>(L, C, xa, Vec<T>::x(C), b, x, nullptr, o.nu2, s, add);
     return;
   }
   smooth<T>(L, x, b, o.nu1, s, xz);
@@ -2012,9 +2014,10 @@ static int64_t box_bytes(ebmg_problem_s* P, int cycles, int iters) {
 
 // deterministic dot product into device scalar slot `slot`
 template <typename T>
-static void dot_dev(DevProblem& D, const T* a, const T* b, int64_t n, int slot, hipStream_t s) {
+static void dot_dev(DevProblem& D, const T* a, const T* b, int64_t n, int slot, hipStream_t s, bool publish = false) {
   hipLaunchKernelGGL((k_dot_partial<T>), dim3(kNormBlocks), dim3(kBlock), 0, s, a, b, n, D.part.p);
-  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, D.part.p, kNormBlocks, 1, D.scal.p + slot);
+  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, D.part.p, kNormBlocks, 1, D.scal.p + slot,
+                     (int)DOT_ONLY, D.scal.p, (int)SC_NUM, publish ? D.host_scal : nullptr);
   HIPCHECK(hipGetLastError());
 }
 
@@ -2049,15 +2052,27 @@ static void graph_run(hipGraphExec_t& exec, hipStream_t s, F&& body) {
   HIPCHECK(hipGraphLaunch(exec, s));
 }
 
-static void fetch_scalars(DevProblem& D, hipStream_t s) {
-  HIPCHECK(hipMemcpyAsync(D.host_scal, D.scal.p, SC_NUM * sizeof(double), hipMemcpyDeviceToHost, s));
+// The scalars a k_dot_final launch publishes to host[0, n), with a 1 in
+// host[n]: arm before that launch is queued, await after. The wait looks at
+// the memory for at most some hundred microseconds and then leaves the wait to
+// the runtime, so long solves do not hold a core.
+static void arm_scalars(double* host, int n) { *(volatile double*)(host + n) = 0.0; }
+static void await_scalars(const double* host, int n, hipStream_t s) {
+  for (int k = 0; k < 4096; ++k) {
+    if (*(const volatile double*)(host + n) != 0.0) {
+      std::atomic_thread_fence(std::memory_order_acquire);
+      return;
+    }
+    __builtin_ia32_pause();
+  }
   HIPCHECK(hipStreamSynchronize(s));
 }
 
 template <typename T>
 static double norm2(DevProblem& D, const T* r, int64_t n, hipStream_t s) {
-  dot_dev<T>(D, r, r, n, SC_RR, s);
-  fetch_scalars(D, s);
+  arm_scalars(D.host_scal, SC_NUM);
+  dot_dev<T>(D, r, r, n, SC_RR, s, true);
+  await_scalars(D.host_scal, SC_NUM, s);
   return std::sqrt(D.host_scal[SC_RR]);
 }
 
@@ -2138,16 +2153,18 @@ static void efield(ebmg_problem_s* P, const double* x, const double* x2, const d
 // Right-preconditioned BiCGStab with the V-cycle as preconditioner; all
 // scalars stay on the device, one host synchronisation per iteration for the
 // convergence test. On entry L.x64 holds phi, L.r64 the residual b - A phi.
-// out = A x on level 0 (x of type Z, widened exactly), with the dot products
+// out = A x (MODE 0: b - A x) on level 0 (x of type Z, widened exactly), with
+// the dot products
 // (da, out) and, for ndot = 2, (out, out) into device slots slot, slot + 1,
 // from per-block partials of the same launches
-template <typename Z>
-static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da, int ndot, int slot, hipStream_t s) {
+template <typename Z, int MODE = 1>
+static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da, int ndot, int slot, hipStream_t s,
+                        int op = DOT_ONLY, bool publish = false, const double* b = nullptr) {
   DevLevel& l = D.lv[0];
   const Tmpl<double>& tp = l.t64;
   int64_t pt = matvec_blocks(l);
   if (l.dim == 3 && l.N >= kResidZMMin) {
-    const bool pair = pair_ok(l) && al2(x) && al2(out) && al2(da);
+    const bool pair = pair_ok(l) && al2(x) && al2(out) && al2(da) && al2(b);
     const dim3 g((unsigned)(pair ? zp_resid_blocks(l) : zm_resid_blocks(l)));
     const int kz = pair ? zp_planes(l) : zm_planes(l);
     const int64_t G = (int64_t)g.x;
@@ -2164,41 +2181,41 @@ static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da
     if ((int64_t)ndot * pt > D.part.n) throw DeviceError("matrix-vector partials exceed their buffer");
     if (pair) {
       if (ndot == 1)
-        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 1>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
+        hipLaunchKernelGGL((k_resid_zp3<double, MODE, Z, 1>), g, dim3(64, kRPY), 0, s, l.tag.p, x, b, out, tp, kz, da,
                            D.part.p, pt);
       else
-        hipLaunchKernelGGL((k_resid_zp3<double, 1, Z, 2>), g, dim3(64, kRPY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
+        hipLaunchKernelGGL((k_resid_zp3<double, MODE, Z, 2>), g, dim3(64, kRPY), 0, s, l.tag.p, x, b, out, tp, kz, da,
                            D.part.p, pt);
     } else if (ndot == 1) {
-      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 1>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
+      hipLaunchKernelGGL((k_resid_zm3<double, MODE, Z, 1>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, b, out, tp, kz, da,
                          D.part.p, pt);
     } else {
-      hipLaunchKernelGGL((k_resid_zm3<double, 1, Z, 2>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, nullptr, out, tp, kz, da,
+      hipLaunchKernelGGL((k_resid_zm3<double, MODE, Z, 2>), g, dim3(kRZX, kRZY), 0, s, l.tag.p, x, b, out, tp, kz, da,
                          D.part.p, pt);
     }
     if (sl) {
       const BLev<double> L = make_blev<double>(l);
       if (ndot == 1)
-        hipLaunchKernelGGL((k_resid_irr_sl<double, 1, Z, 1>), dim3((unsigned)(nb0 + nb1)), dim3(kRowBlock), 0, s, L, nb0,
-                           x, nullptr, out, da, D.part.p, pt, G);
+        hipLaunchKernelGGL((k_resid_irr_sl<double, MODE, Z, 1>), dim3((unsigned)(nb0 + nb1)), dim3(kRowBlock), 0, s, L, nb0,
+                           x, b, out, da, D.part.p, pt, G);
       else
-        hipLaunchKernelGGL((k_resid_irr_sl<double, 1, Z, 2>), dim3((unsigned)(nb0 + nb1)), dim3(kRowBlock), 0, s, L, nb0,
-                           x, nullptr, out, da, D.part.p, pt, G);
+        hipLaunchKernelGGL((k_resid_irr_sl<double, MODE, Z, 2>), dim3((unsigned)(nb0 + nb1)), dim3(kRowBlock), 0, s, L, nb0,
+                           x, b, out, da, D.part.p, pt, G);
     } else if (l.R > 0) {
       if (ndot == 1)
-        hipLaunchKernelGGL((k_resid_irr<double, 1, Z, 1>), dim3(nblk_sub(l.R)), dim3(kBlock), 0, s, (int)l.R,
-                           l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, x, nullptr, out, da, D.part.p, pt,
+        hipLaunchKernelGGL((k_resid_irr<double, MODE, Z, 1>), dim3(nblk_sub(l.R)), dim3(kBlock), 0, s, (int)l.R,
+                           l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, x, b, out, da, D.part.p, pt,
                            G);
       else
-        hipLaunchKernelGGL((k_resid_irr<double, 1, Z, 2>), dim3(nblk_sub(l.R)), dim3(kBlock), 0, s, (int)l.R,
-                           l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, x, nullptr, out, da, D.part.p, pt,
+        hipLaunchKernelGGL((k_resid_irr<double, MODE, Z, 2>), dim3(nblk_sub(l.R)), dim3(kBlock), 0, s, (int)l.R,
+                           l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, x, b, out, da, D.part.p, pt,
                            G);
     }
   } else {
     const unsigned nbc = nblk(l.N);
     const dim3 g(nbc + nblk_sub(l.R));
 #define MV_ALL(DIM, ND)                                                                                           \
-  hipLaunchKernelGGL((k_resid_all<double, DIM, 1, Z, ND>), g, dim3(kBlock), 0, s, l.tag.p, x, nullptr, out, tp,   \
+  hipLaunchKernelGGL((k_resid_all<double, DIM, MODE, Z, ND>), g, dim3(kBlock), 0, s, l.tag.p, x, b, out, tp,   \
                      nbc, (int)l.R, l.irow_dof.p, l.rp.p, l.col.p, l.val64.p, l.diag64.p, da, D.part.p, pt)
     if (l.dim == 3) {
       if (ndot == 1) MV_ALL(3, 1); else MV_ALL(3, 2);
@@ -2207,7 +2224,8 @@ static void matvec_dots(DevProblem& D, const Z* x, double* out, const double* da
     }
 #undef MV_ALL
   }
-  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, D.part.p, (int)pt, ndot, D.scal.p + slot);
+  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, D.part.p, (int)pt, ndot, D.scal.p + slot, op,
+                     D.scal.p, (int)SC_NUM, publish ? D.host_scal : nullptr);
   HIPCHECK(hipGetLastError());
 }
 
@@ -2255,26 +2273,26 @@ static ebmg_status bicgstab_t(DevProblem& D, const Options& o, double bn, double
   auto iteration = [&](hipStream_t q) {
     hipLaunchKernelGGL((k_bicg_p2<Z>), dim3(nb), dim3(kBlock), 0, q, p, r, v, D.scal.p, nd, bf, zin ? nullptr : ph);
     vcyc(ph, p, q);
-    matvec_dots<Z>(D, ph, v, rh, 1, SC_RV, q);
-    hipLaunchKernelGGL(k_sc_alpha, dim3(1), dim3(1), 0, q, D.scal.p);
+    matvec_dots<Z>(D, ph, v, rh, 1, SC_RV, q, DOT_ALPHA);
     hipLaunchKernelGGL((k_bicg_s2<Z>), dim3(nb), dim3(kBlock), 0, q, sv, r, v, D.scal.p, nd, bf, zin ? nullptr : sh);
     vcyc(sh, sv, q);
-    matvec_dots<Z>(D, sh, t, sv, 2, SC_TS, q);
-    hipLaunchKernelGGL(k_sc_omega, dim3(1), dim3(1), 0, q, D.scal.p);
+    matvec_dots<Z>(D, sh, t, sv, 2, SC_TS, q, DOT_OMEGA);
     hipLaunchKernelGGL((k_bicg_xr2<Z>), dim3(kNormBlocks), dim3(kBlock), 0, q, x, r, ph, sh, sv, t, rh, D.scal.p, nd,
                        D.part.p);
-    hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, q, D.part.p, kNormBlocks, 2, D.scal.p + SC_RHO);
+    hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, q, D.part.p, kNormBlocks, 2, D.scal.p + SC_RHO,
+                       (int)DOT_ONLY, D.scal.p, (int)SC_NUM, D.host_scal);
     HIPCHECK(hipGetLastError());
   };
   restart(r0, r0 == L.b64.p);
   int restarts = 0;
   while (rel > rtol) {
     if (cyc + 2 > max_cycles) return EBMG_ERR_NOCONV;
+    arm_scalars(D.host_scal, SC_NUM);
     if (o.graphs == 0 && !D.timing())
       graph_run(D.g_krylov, s, iteration);
     else
       iteration(s);
-    fetch_scalars(D, s);
+    await_scalars(D.host_scal, SC_NUM, s);
     cyc += 2;
     ++info.outer_iters;
     const double* h = D.host_scal;
@@ -2369,24 +2387,33 @@ static ebmg_status solve(ebmg_problem_s* P, const double* rho, const double* sig
           if (!zin) fill<float>(L.x32.p, nd, 0.0f, q);
           vcycle<float>(D, H.opt, 0, q, L.x32.p, L.b32.p, zin);
           hipLaunchKernelGGL(k_add_f32, dim3(nblk(nd)), dim3(kBlock), 0, q, L.x64.p, L.x32.p, nd);
+        } else if (zero_start<double>(D, H.opt) && tiled(D, H.opt, 0)) {
+          // a tiled level 0 starts from zero: the correction of x for r
+          vcycle<double>(D, H.opt, 0, q, L.x64.p, L.r64.p, true, true);
         } else {
           vcycle<double>(D, H.opt, 0, q, L.x64.p, L.b64.p);
         }
-        residual<double, 0>(L, L.x64.p, L.b64.p, L.r64.p, q);
-        dot_dev<double>(D, L.r64.p, L.r64.p, nd, SC_RR, q);
+        // r = b - A x with its norm: b . r (not used) into SC_RHO, r . r into SC_RR
+        if (!D.timing()) {
+          matvec_dots<double, 0>(D, L.x64.p, L.r64.p, L.b64.p, 2, SC_RHO, q, DOT_ONLY, true, L.b64.p);
+        } else {   // residual launches timed by themselves
+          residual<double, 0>(L, L.x64.p, L.b64.p, L.r64.p, q);
+          dot_dev<double>(D, L.r64.p, L.r64.p, nd, SC_RR, q, true);
+        }
       };
       while (rel > rtol) {
         if (cyc >= max_cycles) {
           st = EBMG_ERR_NOCONV;
           break;
         }
+        arm_scalars(D.host_scal, SC_NUM);
         if (H.opt.graphs == 0 && !D.timing())
           graph_run(D.g_plain, s, cycle);
         else
           cycle(s);
         if (mixed) ++loc.outer_iters;
         ++cyc;
-        fetch_scalars(D, s);
+        await_scalars(D.host_scal, SC_NUM, s);
         double nrel = std::sqrt(D.host_scal[SC_RR]) / bn;
         if (loc.n_hist < 64) loc.hist[loc.n_hist++] = nrel;
         if (!std::isfinite(nrel) || nrel > 1e6) {
@@ -3194,7 +3221,8 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
 
 static double amr_dot(ebmg_amr_s* A, const double* a, const double* b, hipStream_t s) {
   hipLaunchKernelGGL((k_dot_partial<double>), dim3(kNormBlocks), dim3(kBlock), 0, s, a, b, A->ntot, A->part.p);
-  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, A->part.p, kNormBlocks, 1, A->scal.p);
+  hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, A->part.p, kNormBlocks, 1, A->scal.p, (int)DOT_ONLY,
+                     A->scal.p, 0, (double*)nullptr);
   HIPCHECK(hipGetLastError());
   double h = 0;
   HIPCHECK(hipMemcpyAsync(&h, A->scal.p, sizeof(double), hipMemcpyDeviceToHost, s));

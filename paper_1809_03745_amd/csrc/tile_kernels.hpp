@@ -91,11 +91,12 @@ __device__ __forceinline__ T tile_rdiag(const Tmpl<T>& tp, int p, int i, int j, 
 }
 
 // PRE: x = 0, `phases` colour phases, xo = x, bc = restriction of b - A x.
-// else: x = xin + P ec, `phases` colour phases, xo = x.
+// else: x = xin + P ec, `phases` colour phases, xo = x (add: xo += x).
 template <typename T, int DIM, int H, bool PRE, bool ROWS>
 __global__ void __launch_bounds__((TileDim<DIM, H>::NT), (H == 12 || (DIM == 3 && !ROWS) ? 8 : 4)) k_tile(TileView<T> V, const T* __restrict__ xin,
                                                            const T* __restrict__ ec, const T* __restrict__ b,
-                                                           T* __restrict__ xo, T* __restrict__ bc, int phases) {
+                                                           T* __restrict__ xo, T* __restrict__ bc, int phases,
+                                                           bool add) {
   using D = TileDim<DIM, H>;
   constexpr int E = D::E, NT = D::NT, NP = D::NP, PAD = D::PAD, HX = E / 2;
   constexpr int RM = ROWS ? kTileRows : 1;
@@ -265,7 +266,7 @@ __global__ void __launch_bounds__((TileDim<DIM, H>::NT), (H == 12 || (DIM == 3 &
       rq[s][u] = 0;
       if (!core || p == 4) continue;
       const T xv = xs[m];
-      xo[c + u] = xv;
+      xo[c + u] = !PRE && add ? xo[c + u] + xv : xv;
       if (PRE && p <= 1) {
         T sm = 0;
         T dg = tp.M(p);
@@ -285,7 +286,10 @@ __global__ void __launch_bounds__((TileDim<DIM, H>::NT), (H == 12 || (DIM == 3 &
     // second-phase unknowns out
     for (int q = t; q < nr; q += NT) {
       const int loc = (int)(rbit[q] & 8191u);
-      if (loc >= D::NE && (rbit[q] >> 31)) xo[rows[q].dof] = xs[loc];
+      if (loc >= D::NE && (rbit[q] >> 31)) {
+        T* o = xo + rows[q].dof;
+        *o = !PRE && add ? *o + xs[loc] : xs[loc];
+      }
     }
   }
   if (!PRE) return;

@@ -101,3 +101,23 @@ def test_one_iteration(ctx, name, nu1, nu2, prec):
     want = alpha * p + (w @ s) / (w @ w) * z
     assert np.linalg.norm(x - want) <= (1e-10 if prec == 0 else 1e-4) * np.linalg.norm(want)
     P.release()
+
+
+@pytest.mark.parametrize("name", ["box 2d 49", "box 2d 73", "box 3d 17", "box 3d 40"])
+def test_one_refinement(ctx, name):
+    """Plain refinement in FP64, where a tiled level 0 adds its result to x."""
+    print("tile refinement", name, flush=True)
+    pr = CASES[name]()
+    P = ebmg.Problem(ctx, pr, precision=0, smoother=4, tail=1, krylov=1)
+    M, A = _vcycle(P, pr, 2, 2)
+    b = P.rhs()
+    phi = torch.zeros(P.N, dtype=torch.float64, device=DEV)
+    rho = torch.tensor(np.ascontiguousarray(pr.rho).ravel(), dtype=torch.float64, device=DEV)
+    x = np.zeros_like(b)
+    for cycles in (1, 2):
+        x = x + M(b - A @ x)
+        _, info = P.solve(rho, phi.zero_(), rtol=1e-14, max_cycles=cycles, check=False)
+        assert np.linalg.norm(phi.cpu().numpy() - x) <= 1e-10 * np.linalg.norm(x)
+        rel = np.linalg.norm(b - A @ x) / np.linalg.norm(b)
+        assert abs(info["rel_residual"] - rel) <= 1e-8 * rel
+    P.release()
