@@ -13,19 +13,23 @@
 namespace ebmg {
 
 // y[row[r]] += sum_e w[e] (col[e] >= 0 ? xs[col[e]] : xo[-col[e] - 1]):
-// one thread per row (rows are distinct, so no two threads write one entry)
+// kAmrLanes lanes per row (rows are distinct, so no two write one entry). A
+// launch has a few thousand rows and waits on the chain column -> value; a
+// thread per row took its entries one after the other (10 us a launch).
+constexpr int kAmrLanes = 8;
 __global__ void __launch_bounds__(256) k_amr_rows(int64_t nrow, const int64_t* __restrict__ row,
                                                   const int64_t* __restrict__ ptr, const int64_t* __restrict__ col,
                                                   const double* __restrict__ w, const double* __restrict__ xs,
                                                   const double* __restrict__ xo, double* __restrict__ y) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t r = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kAmrLanes;
   if (r >= nrow) return;
   double s = 0.0;
-  for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
+  for (int64_t e = ptr[r] + threadIdx.x % kAmrLanes; e < ptr[r + 1]; e += kAmrLanes) {
     const int64_t c = col[e];
     s += w[e] * (c >= 0 ? xs[c] : xo[-c - 1]);
   }
-  y[row[r]] += s;
+  for (int off = kAmrLanes / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kAmrLanes);
+  if (threadIdx.x % kAmrLanes == 0) y[row[r]] += s;
 }
 
 // y[row[r]] = sum_e w[e] x[col[e]]

@@ -381,6 +381,8 @@ struct ebmg_amr_s {
   std::vector<int> order;          // boxes by level, deepest first
   int64_t ntot = 0;
   ebmg::DevBuf<double> x, b, r, rh, p, v, sv, t, ph, sh, rt, y, e, part, scal;
+  double* host_dot = nullptr;      // pinned: the last dot product, and a 1 once it is there
+  hipGraphExec_t g_p = nullptr, g_s = nullptr;   // ph = M p, v = A ph; sh = M sv, t = A sh
   int64_t bytes = 0;
 };
 
@@ -3118,6 +3120,11 @@ static void amr_free(ebmg_amr_s* A) {
     (void)hipSetDevice(A->ctx->device);
     (void)hipStreamSynchronize(A->ctx->stream);
   }
+  if (A->g_p) (void)hipGraphExecDestroy(A->g_p);
+  if (A->g_s) (void)hipGraphExecDestroy(A->g_s);
+  A->g_p = A->g_s = nullptr;
+  if (A->host_dot) (void)hipHostFree(A->host_dot);
+  A->host_dot = nullptr;
   for (auto& k : A->link) k.release();
   A->link.clear();
   for (auto* b : {&A->x, &A->b, &A->r, &A->rh, &A->p, &A->v, &A->sv, &A->t, &A->ph, &A->sh, &A->rt, &A->y, &A->e,
@@ -3141,10 +3148,10 @@ static void amr_apply(ebmg_amr_s* A, const double* x, double* y, hipStream_t s) 
     auto& K = A->link[l];
     const int64_t of = A->off[l], oc = A->off[A->box[l].parent];
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
                          x + of, x + oc, y + of);
     if (K.nc)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
                          x + oc, x + of, y + oc);
     if (K.ncov)
       hipLaunchKernelGGL(k_amr_set, dim3(nblk(K.ncov)), dim3(256), 0, s, K.ncov, K.cov.p, x + oc, y + oc);
@@ -3180,7 +3187,7 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
     precond(A->lev[l]->dev, A->lev[l]->host->opt, rt + of, z + of, s);
     residual<double, 1>(A->lev[l]->dev.lv[0], z + of, nullptr, y + of, s);
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
                          z + of, z + oc, y + of);
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, rt + of, -1.0, y + of, y + of);
     if (K.nr)
@@ -3188,7 +3195,7 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
                          y + of, rt + oc);
     if (K.nc) {
       fill<double>(y + oc, mc, 0.0, s);
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
                          z + oc, z + of, y + oc);
       hipLaunchKernelGGL(k_amr_lin, dim3(nblk(mc)), dim3(256), 0, s, mc, 1.0, rt + oc, -1.0, y + oc, rt + oc);
     }
@@ -3204,7 +3211,7 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, z + of, 1.0, e + of, z + of);
     residual<double, 1>(A->lev[l]->dev.lv[0], z + of, nullptr, y + of, s);
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
                          z + of, z + oc, y + of);
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, rt + of, -1.0, y + of, y + of);
     precond(A->lev[l]->dev, A->lev[l]->host->opt, y + of, e + of, s);
@@ -3221,23 +3228,35 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
 
 static double amr_dot(ebmg_amr_s* A, const double* a, const double* b, hipStream_t s) {
   hipLaunchKernelGGL((k_dot_partial<double>), dim3(kNormBlocks), dim3(kBlock), 0, s, a, b, A->ntot, A->part.p);
+  arm_scalars(A->host_dot, 1);
   hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(kBlock), 0, s, A->part.p, kNormBlocks, 1, A->scal.p, (int)DOT_ONLY,
-                     A->scal.p, 0, (double*)nullptr);
+                     A->scal.p, 1, A->host_dot);
   HIPCHECK(hipGetLastError());
-  double h = 0;
-  HIPCHECK(hipMemcpyAsync(&h, A->scal.p, sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  return h;
+  await_scalars(A->host_dot, 1, s);
+  return A->host_dot[0];
 }
 
 // right-preconditioned BiCGStab over the composite vector, FP64, from the
-// guess in A->x; one host round trip per dot product
+// guess in A->x; one host round trip per dot product. The two applications of
+// the preconditioner and the operator, nearly all of an iteration's launches
+// (about a hundred each), are graphs: launched one by one the host is the
+// slower side
 static ebmg_status amr_bicgstab(ebmg_amr_s* A, double rtol, int maxit, double& bn, double& rel, int& iters,
                                 hipStream_t s) {
   const int64_t n = A->ntot;
   const dim3 g(nblk(n)), blk(256);
   double *x = A->x.p, *b = A->b.p, *r = A->r.p, *rh = A->rh.p, *p = A->p.p, *v = A->v.p, *sv = A->sv.p,
          *t = A->t.p, *ph = A->ph.p, *sh = A->sh.p, *y = A->y.p;
+  auto apply = [&](hipGraphExec_t& g, const double* u, double* mu, double* au) {
+    auto body = [&](hipStream_t q) {
+      amr_precond(A, u, mu, q);
+      amr_apply(A, mu, au, q);
+    };
+    if (A->lev[0]->host->opt.graphs == 0)
+      graph_run(g, s, body);
+    else
+      body(s);
+  };
   iters = 0;
   bn = std::sqrt(amr_dot(A, b, b, s));
   if (!(bn > 0)) {
@@ -3260,8 +3279,7 @@ static ebmg_status amr_bicgstab(ebmg_amr_s* A, double rtol, int maxit, double& b
     if (rho == 0.0) return EBMG_ERR_NOCONV;
     const double beta = (rho / rho_old) * (alpha / omega);
     hipLaunchKernelGGL(k_amr_p, g, blk, 0, s, n, r, beta, omega, v, p);
-    amr_precond(A, p, ph, s);
-    amr_apply(A, ph, v, s);
+    apply(A->g_p, p, ph, v);
     alpha = rho / amr_dot(A, rh, v, s);
     hipLaunchKernelGGL(k_amr_lin, g, blk, 0, s, n, 1.0, r, -alpha, v, sv);
     const double sn = std::sqrt(amr_dot(A, sv, sv, s)) / bn;
@@ -3272,8 +3290,7 @@ static ebmg_status amr_bicgstab(ebmg_amr_s* A, double rtol, int maxit, double& b
       rel = sn;
       return EBMG_OK;
     }
-    amr_precond(A, sv, sh, s);
-    amr_apply(A, sh, t, s);
+    apply(A->g_s, sv, sh, t);
     const double tt = amr_dot(A, t, t, s);
     omega = tt > 0 ? amr_dot(A, t, sv, s) / tt : 0.0;
     hipLaunchKernelGGL(k_amr_xr, g, blk, 0, s, n, alpha, ph, omega, sh, sv, t, x, r);
@@ -4885,6 +4902,7 @@ ebmg_status ebmg_setup_amr(ebmg_ctx ctx, int32_t nbox, const ebmg_box* boxes, co
       b->alloc(A->ntot, by);
     A->part.alloc(kNormBlocks, by);
     A->scal.alloc(8, by);
+    HIPCHECK(hipHostMalloc((void**)&A->host_dot, 2 * sizeof(double), hipHostMallocCoherent));
     for (auto* b : {&A->x, &A->b, &A->r, &A->rh, &A->p, &A->v, &A->sv, &A->t, &A->ph, &A->sh, &A->rt, &A->y, &A->e})
       fill<double>(b->p, A->ntot, 0.0, s);
     HIPCHECK(hipStreamSynchronize(s));
