@@ -456,8 +456,8 @@ ebmg_status ebmg_kernel_timing(ebmg_problem pb, int32_t which, int32_t level, in
  * new absorption kappa): alpha, beta, a_gas, a_diel, b_gas in opt and the
  * boundary data in bc (values and Robin a1/a2; kinds must equal those given
  * at setup). Every other option must equal the setup's. The template
- * constants of all levels and the bottom inverse are rebuilt on the host and
- * re-sent; the device hierarchy is kept. ERR_ARG if the problem does not
+ * constants of all levels are rebuilt on the host and re-sent, the bottom
+ * inverse on the device; the hierarchy is kept. ERR_ARG if the problem does not
  * qualify. Not to be called while a solve on the problem is running. */
 ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, const ebmg_domain_bc* bc);
 

@@ -6,9 +6,11 @@
 // and one exchanged row through LDS), the other columns follow in one
 // matrix product per panel over the whole chip, from one buffer into the
 // other, which also applies the panel's row exchanges. The panels' serial
-// columns bound it (some 0.4 us each). An unblocked elimination on one host
-// core took 35 ms for the 512 unknowns of an 8^3 bottom level, most of a
-// served request that brings new coefficients; this takes 0.5 ms.
+// columns bound it. Diagonally dominant matrices (plain boxes) need no pivot
+// search: their panels cost a fifth (18 us against 84 at n = 512). An unblocked elimination on one host core
+// took 35 ms for the 512 unknowns of an 8^3 bottom level, most of a served
+// request that brings new coefficients; this takes 1.5 ms, and 0.5 ms where no
+// pivots are searched.
 #pragma once
 
 #include "block_engine.hpp"
@@ -71,7 +73,7 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_panel(const double* __restr
                                                           int n, int k0, int* __restrict__ src,
                                                           const int* __restrict__ perm_in, int* __restrict__ perm_out,
                                                           int* __restrict__ flag) {
-  static_assert(NB * U == 32, "32 values of the panel per thread");
+  static_assert(NB * U <= 32, "at most 32 values of the panel per thread");
   __shared__ double prow[2][NB], krow[2][NB];
   __shared__ int sidx[2][2];
   __shared__ uint32_t wmax[2][kInvThreads / 64];
@@ -153,6 +155,50 @@ __global__ void __launch_bounds__(kInvThreads) k_inv_panel(const double* __restr
       if (c < nb) Y[(int64_t)r * n + k0 + c] = a[u][c];
     src[r] = from[u];
     perm_out[r] = perm_in ? perm_in[from[u]] : from[u];
+  }
+}
+
+// The same panel without exchanges, for a diagonally dominant matrix (the
+// pivots then stay the diagonal's and no entry grows beyond twice the largest):
+// only the NB x NB diagonal block is eliminated column by column, one thread an
+// entry, by every workgroup for itself, and each takes its share of the panel's
+// rows as a product with the block's inverse. The panel above passes all n rows
+// through each column (2.6 us a column at n = 512: 84 us a panel).
+template <int NB>
+__global__ void __launch_bounds__(NB * NB) k_inv_panel_dd(const double* __restrict__ X, double* __restrict__ Y, int n,
+                                                        int k0, int* __restrict__ src, int* __restrict__ perm,
+                                                        int* __restrict__ flag) {
+  __shared__ double prow[2][NB], pcol[2][NB], S[NB][NB + 1], XR[NB][NB + 1];
+  const int i = threadIdx.x / NB, j = threadIdx.x % NB;
+  const int nb = min(NB, n - k0);
+  const int r = blockIdx.x * NB + i;   // the panel row of this thread
+  XR[i][j] = r < n && j < nb ? X[(int64_t)r * n + k0 + j] : 0.0;
+  double v = i < nb && j < nb ? X[(int64_t)(k0 + i) * n + k0 + j] : (i == j ? 1.0 : 0.0);
+  for (int c = 0; c < nb; ++c) {
+    const int buf = c & 1;
+    if (i == c) prow[buf][j] = v;
+    if (j == c) pcol[buf][i] = v;
+    __syncthreads();
+    const double pivot = prow[buf][c];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !(pivot != 0.0)) *flag = 1;
+    const double pv = 1.0 / pivot;
+    const double row = j == c ? pv : prow[buf][j] * pv;
+    v = i == c ? row : (j == c ? 0.0 : v) - pcol[buf][i] * row;
+  }
+  S[i][j] = v;
+  __syncthreads();
+  if (r >= n) return;
+  double e = 0.0;
+  if (r >= k0 && r < k0 + nb) {
+    e = S[r - k0][j];
+  } else {
+#pragma unroll 8
+    for (int c = 0; c < NB; ++c) e -= XR[i][c] * S[c][j];
+  }
+  if (j < nb) Y[(int64_t)r * n + k0 + j] = e;
+  if (j == 0) {
+    src[r] = r;
+    perm[r] = r;
   }
 }
 

@@ -954,9 +954,26 @@ static void upload_bottom_krylov(DevProblem& D, hipStream_t s) {
   HIPCHECK(hipStreamSynchronize(s));
 }
 
+// Whether no row's off-diagonal entries outweigh its diagonal, and some row's
+// fall clearly short of it (plain boxes with a mass or a value on some face;
+// elimination in the given order is then as safe as with pivoting, and the
+// singular pure-flux box keeps the search and its refusal).
+static bool row_dominant(const Level& L) {
+  std::vector<std::pair<int64_t, double>> row;
+  bool strict = false;
+  for (int64_t q = 0; q < L.ndof(); ++q) {
+    double diag = 0, off = 0;
+    L.row(q, diag, row);   // (the row sum first: the diagonal entry comes without it)
+    for (const auto& e : row) (e.first == q ? diag : off) += e.first == q ? e.second : std::abs(e.second);
+    if (!(off <= std::abs(diag) * (1 + 1e-12))) return false;
+    strict = strict || off < 0.99 * std::abs(diag);
+  }
+  return strict;
+}
+
 // The dense inverse of the bottom level into D.bottom, from the level's
 // resident rows. Waits for it.
-static void device_bottom(DevProblem& D, bool keep_work, hipStream_t s) {
+static void device_bottom(DevProblem& D, const Level& H, bool keep_work, hipStream_t s) {
   DevLevel& B = D.lv.back();
   const int n = (int)D.bottom_n;
   if (!D.bottom.p) D.bottom.alloc((int64_t)n * n, D.bytes);
@@ -972,16 +989,23 @@ static void device_bottom(DevProblem& D, bool keep_work, hipStream_t s) {
     hipLaunchKernelGGL((k_dense_rows<3>), gr, dim3(256), 0, s, L, X);
   else
     hipLaunchKernelGGL((k_dense_rows<2>), gr, dim3(256), 0, s, L, X);
+  const bool dominant = row_dominant(H);
   // panel width by the rows a thread of the panel's workgroup holds
-  const int nb = n <= kInvThreads ? 32 : n <= 2 * kInvThreads ? 16 : 8;
+  const int nb = dominant || n <= kInvThreads ? 32 : 8;
   const unsigned gt = (unsigned)((n + kInvTile - 1) / kInvTile);
   const int32_t* pin = nullptr;
   for (int k0 = 0; k0 < n; k0 += nb) {
-#define INV_PANEL(NB, U)                                                                                          hipLaunchKernelGGL((k_inv_panel<NB, U>), dim3(1), dim3(kInvThreads), 0, s, X, Y, n, k0, src, pin, perm, flag);   hipLaunchKernelGGL((k_inv_update<NB>), dim3(gt, gt), dim3(256), 0, s, X, Y, n, k0, src)
-    if (nb == 32) {
+#define INV_PANEL(NB, U)                                                                                         \
+  hipLaunchKernelGGL((k_inv_panel<NB, U>), dim3(1), dim3(kInvThreads), 0, s, X, Y, n, k0, src, pin, perm, flag); \
+  hipLaunchKernelGGL((k_inv_update<NB>), dim3(gt, gt), dim3(256), 0, s, X, Y, n, k0, src)
+    if (dominant) {
+      hipLaunchKernelGGL((k_inv_panel_dd<32>), dim3((unsigned)((n + 31) / 32)), dim3(32 * 32), 0, s, X, Y, n, k0, src,
+                         perm, flag);
+      hipLaunchKernelGGL((k_inv_update<32>), dim3(gt, gt), dim3(256), 0, s, X, Y, n, k0, src);
+    } else if (nb == 32) {
       INV_PANEL(32, 1);
-    } else if (nb == 16) {
-      INV_PANEL(16, 2);
+    } else if (n <= 2 * kInvThreads) {
+      INV_PANEL(8, 2);
     } else {
       INV_PANEL(8, 4);
     }
@@ -1415,7 +1439,7 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
   }
   D.bottom_n = H.bottom_n;
   if (D.bottom_n <= kBottomMax)
-    device_bottom(D, !batch_box && recoefficientable(H), s);
+    device_bottom(D, H.levels.back(), !batch_box && recoefficientable(H), s);
   else
     upload_bottom_krylov(D, s);
   // rhs data
@@ -4378,7 +4402,7 @@ ebmg_status ebmg_set_coefficients(ebmg_problem pb, const ebmg_options* opt, cons
       if (!H.levels[l].irow_dof.empty()) update_row_values(D.lv[l], H.levels[l], s);
     }
     if (D.bottom.p)
-      device_bottom(D, true, s);
+      device_bottom(D, H.levels.back(), true, s);
     else
       upload_bottom_krylov(D, s);   // its view holds the bottom level's template constants
     // the one-workgroup engine keeps copies of the templates in its level views

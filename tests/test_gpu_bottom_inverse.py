@@ -3,6 +3,8 @@
 the inverse, over the panel widths and the remainders of panels and tiles.
 One cycle has to reach 1e-11 relative residual (the inverse of a matrix of
 condition below 1e4 leaves a few 1e-13), and the oracle's solution to 1e-10."""
+import dataclasses
+
 import numpy as np
 import pytest
 
@@ -35,7 +37,7 @@ def plain(nx, ny):
                      [1.0] * 6, rho=rho, name=f"plain-{nx}x{ny}")
 
 
-# unknowns: 1, 6, 31, 32, 33 | 992, 1024 (32-wide panels) | 1025, 2048 (16) | 2050, 4096 (8)
+# unknowns: 1, 6, 31, 32, 33 | 992, 1024 (one panel row a thread) | 1025, 2048 (two) | 2050, 4096 (four)
 PLAIN = [(1, 1), (2, 3), (1, 31), (4, 8), (3, 11), (31, 32), (32, 32), (25, 41), (32, 64), (41, 50), (64, 64)]
 
 
@@ -100,3 +102,23 @@ def test_new_coefficients(ctx):
     assert all(np.array_equal(out[0], o) for o in out[1:])
     P.release()
     Q.release()
+
+
+@pytest.mark.parametrize("nx,ny", PLAIN[1:])
+def test_plain_box_with_pivots(ctx, nx, ny):
+    """A negative mass (above the lowest eigenvalue's) takes the diagonal below
+    the off-diagonal sum, so that pivots are searched."""
+    print("bottom inverse with pivots", nx, ny, flush=True)
+    pr = dataclasses.replace(plain(nx, ny), alpha=1.0, a_gas=-3.0, a_diel=-3.0)
+    S = assemble(pr)
+    A = abs(S.A)
+    assert min(nx, ny) < 8 or (A.sum(axis=1).A1 - 2 * A.diagonal()).max() > 0
+    xs = solve_splu(S.A, S.b)
+    P = ebmg.Problem(ctx, pr, bottom_max_dof=4096)
+    assert P.levels == 1
+    phi = torch.zeros(P.N, dtype=torch.float64, device=DEV)
+    torch.cuda.synchronize()
+    st, info = P.solve(_t(pr.rho), phi, rtol=1e-11, max_cycles=1, check=False)
+    assert st == ebmg.OK and info["cycles"] == 1
+    assert np.linalg.norm(phi.cpu().numpy() - xs) <= 1e-10 * np.linalg.norm(xs)
+    P.release()
