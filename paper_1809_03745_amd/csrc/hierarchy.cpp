@@ -252,12 +252,20 @@ void coarse_rows(const Problem& pb, const Level& L, Level& C) {
 // those with missing children are restricted and prolonged by list. Stopping
 // at the first odd extent instead left bottom levels of thousands of
 // unknowns (a 1000^2 box ends at 125^2), whose solve was all but 5 ms of a
-// 0.98 s solve there and 0.32 of 0.33 s at 100^3.
+// 0.98 s solve there and 0.32 of 0.33 s at 100^3. A first odd level that the
+// dense inverse can still take is the bottom: its product costs less than the
+// further levels' launches, and the cycle solves it exactly (488^2 two disks
+// ending at 61^2 instead of 16^2: 2.76 -> 2.23 ms, 72^3 pin 4.81 -> 4.06 ms).
 static bool coarsen(Problem& pb, size_t lf) {
   Level& L = pb.levels[lf];
   const Grid& gf = L.g;
-  for (int d = 0; d < gf.dim; ++d)
+  bool odd = false, even_so_far = true;
+  for (int d = 0; d < gf.dim; ++d) {
     if (gf.n[d] < 4) return false;
+    odd = odd || gf.n[d] % 2;
+    even_so_far = even_so_far && L.fill[d] == 1.0;
+  }
+  if (odd && even_so_far && L.ndof() <= kBottomMax) return false;
   Level C;
   C.g = gf;
   for (int d = 0; d < gf.dim; ++d) {

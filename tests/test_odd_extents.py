@@ -31,10 +31,12 @@ def ragged_pin(n):
 CASES = {
     "sine 50 (25 = odd at level 1)": lambda: W.manufactured_sine(50),
     "sine 99 (odd at every level)": lambda: W.manufactured_sine(99),
+    "sine 150 (75 = odd at level 1)": lambda: W.manufactured_sine(150),
     "eddington 2d 77": lambda: W.eddington(2, 77, 3.0, seed=1),
     "eddington 3d 21": lambda: W.eddington(3, 21, 9.0, seed=1),
     "two disks 101": lambda: W.two_disks(101, seed=3),
     "two disks 90": lambda: W.two_disks(90, seed=3),
+    "two disks 150": lambda: W.two_disks(150, seed=3),
     "pin 21 x 24 x 22": lambda: ragged_pin((21, 24, 22)),
 }
 
@@ -49,14 +51,16 @@ def ctx():
 @pytest.mark.parametrize("name", sorted(CASES))
 def test_hierarchy_reaches_a_small_bottom(name):
     P = ebmg.Problem(ebmg.Context(-1), CASES[name]())
-    assert sum(P.level_size(P.levels - 1)) <= 600
+    # a first odd level of at most 4096 unknowns is the bottom; past one, coarsening goes on
+    ext = CASES[name]().n[0]
+    assert sum(P.level_size(P.levels - 1)) <= (600 if ext in (99, 150, 77, 21, 101) else 4096)
     for lev in range(P.levels):
         tag, prim, _ = P.level_arrays(lev)
         A = P.operator(lev)
         assert np.all(A.diagonal()[:len(tag)][prim >= 0] > 0)
 
 
-@pytest.mark.parametrize("dim,n", [(2, 50), (2, 51), (2, 130), (3, 18), (3, 27)])
+@pytest.mark.parametrize("dim,n", [(2, 50), (2, 51), (2, 130), (2, 150), (3, 18), (3, 27), (3, 34)])
 def test_new_coefficients_equal_new_setup(dim, n):
     """Explicit rows on coarse levels (odd extents) are rebuilt too."""
     c = ebmg.Context(-1)
