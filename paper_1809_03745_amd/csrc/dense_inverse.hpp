@@ -7,10 +7,10 @@
 // matrix product per panel over the whole chip, from one buffer into the
 // other, which also applies the panel's row exchanges. The panels' serial
 // columns bound it. Diagonally dominant matrices (plain boxes) need no pivot
-// search: their panels cost a fifth (18 us against 84 at n = 512). An unblocked elimination on one host core
-// took 35 ms for the 512 unknowns of an 8^3 bottom level, most of a served
-// request that brings new coefficients; this takes 1.5 ms, and 0.5 ms where no
-// pivots are searched.
+// search: their panels cost a fifth (18 us against 84 at n = 512). An
+// unblocked elimination on one host core took 35 ms for the 512 unknowns of an
+// 8^3 bottom level, most of a served request that brings new coefficients;
+// this takes 1.5 ms, and 0.5 ms where no pivots are searched.
 #pragma once
 
 #include "block_engine.hpp"

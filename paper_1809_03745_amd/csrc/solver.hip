@@ -3172,11 +3172,11 @@ static void amr_apply(ebmg_amr_s* A, const double* x, double* y, hipStream_t s) 
     auto& K = A->link[l];
     const int64_t of = A->off[l], oc = A->off[A->box[l].parent];
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
-                         x + of, x + oc, y + of);
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p,
+                         K.fcol.p, K.fw.p, x + of, x + oc, y + of);
     if (K.nc)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
-                         x + oc, x + of, y + oc);
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p,
+                         K.ccol.p, K.cw.p, x + oc, x + of, y + oc);
     if (K.ncov)
       hipLaunchKernelGGL(k_amr_set, dim3(nblk(K.ncov)), dim3(256), 0, s, K.ncov, K.cov.p, x + oc, y + oc);
   }
@@ -3211,16 +3211,16 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
     precond(A->lev[l]->dev, A->lev[l]->host->opt, rt + of, z + of, s);
     residual<double, 1>(A->lev[l]->dev.lv[0], z + of, nullptr, y + of, s);
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
-                         z + of, z + oc, y + of);
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p,
+                         K.fcol.p, K.fw.p, z + of, z + oc, y + of);
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, rt + of, -1.0, y + of, y + of);
     if (K.nr)
       hipLaunchKernelGGL(k_amr_gather, dim3(nblk(K.nr)), dim3(256), 0, s, K.nr, K.rrow.p, K.rptr.p, K.rcol.p, K.rw.p,
                          y + of, rt + oc);
     if (K.nc) {
       fill<double>(y + oc, mc, 0.0, s);
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p, K.ccol.p, K.cw.p,
-                         z + oc, z + of, y + oc);
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nc * kAmrLanes)), dim3(256), 0, s, K.nc, K.crow.p, K.cptr.p,
+                         K.ccol.p, K.cw.p, z + oc, z + of, y + oc);
       hipLaunchKernelGGL(k_amr_lin, dim3(nblk(mc)), dim3(256), 0, s, mc, 1.0, rt + oc, -1.0, y + oc, rt + oc);
     }
   }
@@ -3235,8 +3235,8 @@ static void amr_precond(ebmg_amr_s* A, const double* r, double* z, hipStream_t s
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, z + of, 1.0, e + of, z + of);
     residual<double, 1>(A->lev[l]->dev.lv[0], z + of, nullptr, y + of, s);
     if (K.nf)
-      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p, K.fcol.p, K.fw.p,
-                         z + of, z + oc, y + of);
+      hipLaunchKernelGGL(k_amr_rows, dim3(nblk(K.nf * kAmrLanes)), dim3(256), 0, s, K.nf, K.frow.p, K.fptr.p,
+                         K.fcol.p, K.fw.p, z + of, z + oc, y + of);
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, rt + of, -1.0, y + of, y + of);
     precond(A->lev[l]->dev, A->lev[l]->host->opt, y + of, e + of, s);
     hipLaunchKernelGGL(k_amr_lin, dim3(nblk(m)), dim3(256), 0, s, m, 1.0, z + of, 1.0, e + of, z + of);
