@@ -152,7 +152,11 @@ __device__ __forceinline__ double search_d2(const DevSearchTri& t, double px, do
 // branch. A subtree is entered while any lane's best distance exceeds its box
 // distance, nearer child first by vote, and a triangle is evaluated only if
 // its disc is closer than some lane's best. The distance and the sign come
-// from closest_on_triangle on the winner. Bound by the FP64 arithmetic of the
+// from closest_on_triangle on the winner, the distance from the search itself
+// where that found a clearly smaller one (slivers: evaluating every triangle
+// and taking the least, as the search of one node does, never exceeded the
+// distance to the nearest edge; the winner alone did, by up to 8e-6 on a
+// unit-length prism 1e-6 wide). Bound by the FP64 arithmetic of the
 // tests on large lattices, by the chain of loads along the walk on small ones.
 // One thread per node with a stack and axis-aligned boxes took 4.1 ms for
 // 129^3 nodes of a 6144-triangle pin and 28 ms at 257^3, its lanes diverging
@@ -229,7 +233,11 @@ __global__ void __launch_bounds__(kSdfBlock) k_sdf_mesh(const DevMeshBox* __rest
         const double* r = tri + (int64_t)win * 30;
         double cx, cy, cz;
         int f;
-        d = sqrt(closest_on_triangle(r, px, py, pz, cx, cy, cz, f));
+        // on a sliver either evaluation may place the closest point far along
+        // its length; the smaller distance is the better one (elsewhere they
+        // agree to rounding, and the first is kept)
+        const double d2 = closest_on_triangle(r, px, py, pz, cx, cy, cz, f);
+        d = sqrt(best < d2 * (1.0 - 1e-9) ? best : d2);
         const double* nrm = f == 0 ? r + 9 : (f <= 3 ? r + 12 + 3 * (f - 1) : r + 21 + 3 * (f - 4));
         side = (px - cx) * nrm[0] + (py - cy) * nrm[1] + (pz - cz) * nrm[2];
       }
