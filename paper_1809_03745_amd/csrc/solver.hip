@@ -678,6 +678,8 @@ static BLev<T> make_blev(DevLevel& l) {
 template <typename T>
 static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* x, const T* b, bool xz = false,
                    bool add = false);
+template <typename T>
+static bool from_zero(DevProblem& D, const Options& o);
 
 // Tail autotuner: time a whole V-cycle (on zero vectors) with the one-
 // workgroup engine starting at each level of at most kTailMax unknowns, and
@@ -755,10 +757,13 @@ static void tune_tail(DevProblem& D, const Options& o, hipStream_t s) {
   D.tail_ms.assign(cand.size(), 0.0);
   for (size_t k = 0; k < cand.size(); ++k) {
     D.tail_l0 = cand[k];
-    for (int r = 0; r < 2; ++r) vcycle<T>(D, o, 0, s, x, b);
+    // as a solve runs it: a tiled level 0 only from x = 0 (timed by its
+    // phases, a 64^2 cycle by launches was charged ten launches too many)
+    const bool xz = from_zero<T>(D, o);
+    for (int r = 0; r < 2; ++r) vcycle<T>(D, o, 0, s, x, b, xz);
     const int reps = 5;
     HIPCHECK(hipEventRecord(e0, s));
-    for (int r = 0; r < reps; ++r) vcycle<T>(D, o, 0, s, x, b);
+    for (int r = 0; r < reps; ++r) vcycle<T>(D, o, 0, s, x, b, xz);
     HIPCHECK(hipEventRecord(e1, s));
     HIPCHECK(hipEventSynchronize(e1));
     float ms = 0;
@@ -1868,6 +1873,15 @@ static bool zero_start(DevProblem& D, const Options& o) {
          (tiled(D, o, 0) || (L.dim == 3 && L.fused && L.fvar == 1 && o.nu1 > 0));
 }
 
+// Whether a solve's V-cycles are told that their x is zero: those of the Krylov
+// iteration and of mixed refinement where that spares reading it, those of
+// FP64 refinement (which otherwise cycle on the solution itself) only on a
+// tiled level 0.
+template <typename T>
+static bool from_zero(DevProblem& D, const Options& o) {
+  return zero_start<T>(D, o) && (sizeof(T) == 4 || D.krylov || tiled(D, o, 0));
+}
+
 template <typename T, bool PRE>
 static void launch_tile(DevLevel& l, DevLevel& c, const T* xin, const T* ec, const T* b, T* xo, T* bc, int sweeps,
                         hipStream_t s, bool add = false) {
@@ -2413,7 +2427,7 @@ static ebmg_status solve(ebmg_problem_s* P, const double* rho, const double* sig
           if (!zin) fill<float>(L.x32.p, nd, 0.0f, q);
           vcycle<float>(D, H.opt, 0, q, L.x32.p, L.b32.p, zin);
           hipLaunchKernelGGL(k_add_f32, dim3(nblk(nd)), dim3(kBlock), 0, q, L.x64.p, L.x32.p, nd);
-        } else if (zero_start<double>(D, H.opt) && tiled(D, H.opt, 0)) {
+        } else if (from_zero<double>(D, H.opt)) {
           // a tiled level 0 starts from zero: the correction of x for r
           vcycle<double>(D, H.opt, 0, q, L.x64.p, L.r64.p, true, true);
         } else {
