@@ -2010,12 +2010,16 @@ static void precond(DevProblem& D, const Options& o, const double* r, double* z,
 // value and per row its unknown index, b and diagonal, and write x; the
 // V-cycle residual restricted into the coarse b reads x, b and the tag and
 // writes the coarse b; prolongation reads the coarse correction, x and the
-// tag and writes x; the dense bottom inverse is read once per application.
+// tag and writes x; a tiled level's two launches read b, the tag and the rows
+// once each (the halo comes from the caches), the first writes x and the
+// coarse b, the second reads x and the coarse correction and writes x; the
+// dense bottom inverse is read once per application.
 static double rows_bytes(const DevLevel& l, int vsz) {
   return (double)l.R * (8.0 + 3.0 * vsz) + (double)l.col.n * (4.0 + vsz);
 }
 
-static double vcycle_bytes(const DevProblem& D, const Options& o, int vsz) {
+static double vcycle_bytes(DevProblem& D, const Options& o, int vsz) {
+  const bool zero = vsz == 4 ? from_zero<float>(D, o) : from_zero<double>(D, o);
   double by = 0;
   for (size_t l = 0; l < D.lv.size(); ++l) {
     const DevLevel& L = D.lv[l];
@@ -2025,6 +2029,11 @@ static double vcycle_bytes(const DevProblem& D, const Options& o, int vsz) {
       break;
     }
     const DevLevel& C = D.lv[l + 1];
+    if ((l > 0 || zero) && (D.tail_l0 < 0 || (int)l < D.tail_l0) && tiled(D, o, l)) {
+      by += (double)L.N * (5.0 * vsz + 2.0) + 2.0 * rows_bytes(L, vsz) + 2.0 * (double)(C.N + C.N2) * vsz;
+      if (l == 0 && vsz == 8 && !D.krylov) by += (double)L.N * vsz;   // added to the solution
+      continue;
+    }
     const double sweeps = o.nu1 + o.nu2;
     by += sweeps * ((double)L.N * (3.0 * vsz + 1.0) + rows_bytes(L, vsz));
     by += (double)L.N * (2.0 * vsz + 1.0) + rows_bytes(L, vsz) + (double)(C.N + C.N2) * vsz;   // residual, restriction
@@ -2035,28 +2044,31 @@ static double vcycle_bytes(const DevProblem& D, const Options& o, int vsz) {
 
 // per outer iteration, besides its V-cycles: BiCGStab's vector steps and its
 // two FP64 matrix-vector products (with their dot products), or a refinement
-// cycle's conversions, correction and FP64 residual with its norm
-static double iteration_bytes(const DevProblem& D, const Options& o) {
+// cycle's conversions, correction and FP64 residual (whose norm takes a pass of
+// its own in the batched solver); the correction is cleared where a cycle from
+// zero reads it
+static double iteration_bytes(DevProblem& D, const Options& o, bool norm_pass) {
   const DevLevel& L = D.lv[0];
   const double n = (double)(L.N + L.N2);
   const bool mixed = o.precision == EBMG_MIXED;
   const double zs = mixed ? 4.0 : 8.0;
+  const double clear = (mixed ? zero_start<float>(D, o) : zero_start<double>(D, o)) ? 0.0 : zs;
   const double mv = (double)L.N * 1.0 + n * (zs + 16.0) + rows_bytes(L, 8);
   if (D.krylov)
-    return n * (32.0 + 24.0 + 56.0 + 2.0 * zs + (mixed ? 8.0 : 0.0)) + 2.0 * mv;
-  return n * (mixed ? 12.0 + 4.0 + 20.0 : 0.0) + (double)L.N * 25.0 + rows_bytes(L, 8) + n * 8.0;
+    return n * (32.0 + 24.0 + 56.0 + 2.0 * clear + (mixed ? 8.0 : 0.0)) + 2.0 * mv;
+  return n * (mixed ? 12.0 + clear + 20.0 : 0.0) + (double)L.N * 25.0 + rows_bytes(L, 8) + (norm_pass ? n * 8.0 : 0.0);
 }
 
 // estimated bytes of one box of a batched solve: its cycles and outer
 // iterations as for a single solve, plus its right-hand side and residuals
 static int64_t box_bytes(ebmg_problem_s* P, int cycles, int iters) {
-  const DevProblem& D = P->dev;
+  DevProblem& D = P->dev;
   const DevLevel& L = D.lv[0];
   const Options& o = P->host->opt;
   const double n = (double)(L.N + L.N2);
   double by = (double)L.N * 17.0 + rows_bytes(L, 8) + 2.0 * ((double)L.N * 25.0 + rows_bytes(L, 8) + n * 8.0);
   by += cycles * vcycle_bytes(D, o, o.precision == EBMG_MIXED ? 4 : 8);
-  by += (D.krylov ? iters : cycles) * iteration_bytes(D, o);
+  by += (D.krylov ? iters : cycles) * iteration_bytes(D, o, true);
   return (int64_t)by;
 }
 
@@ -2492,7 +2504,7 @@ static ebmg_status solve(ebmg_problem_s* P, const double* rho, const double* sig
     if (E) by += (double)L.N * (9.0 + 8.0 * L.dim);
     const int vsz = mixed ? 4 : 8;
     by += loc.cycles * vcycle_bytes(D, H.opt, vsz);
-    by += (D.krylov ? loc.outer_iters : loc.cycles) * iteration_bytes(D, H.opt);
+    by += (D.krylov ? loc.outer_iters : loc.cycles) * iteration_bytes(D, H.opt, D.timing());
     loc.est_bytes = (int64_t)by;
   }
   if (info) *info = loc;
