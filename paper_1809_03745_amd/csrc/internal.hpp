@@ -20,6 +20,7 @@ struct ArgError : std::runtime_error {
 };
 
 constexpr double kTiny = 1e-12;
+constexpr int kMaxObj = 64;   // embedded objects of a box
 
 // Uniform box of cells; 2D boxes use n[2] = 1 and k = 0.
 struct Grid {

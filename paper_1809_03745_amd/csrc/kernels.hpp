@@ -1882,13 +1882,9 @@ __global__ void __launch_bounds__(kBlock) k_rhs_reg(const uint8_t* __restrict__ 
 struct FaceVals {
   double v[6];
 };
-// the objects' values of a solve, as a kernel argument (up to kMaxObj of
-// them, else in device memory)
-constexpr int kMaxObj = 64;
+// the objects' values of a solve, as a kernel argument
 struct ObjVals {
-  const double* p;
   double v[kMaxObj];
-  __device__ __forceinline__ double operator[](int k) const { return p ? p[k] : v[k]; }
 };
 
 __global__ void __launch_bounds__(kBlock) k_rhs_irr(int nrows, const int64_t* __restrict__ dof,
@@ -1902,7 +1898,7 @@ __global__ void __launch_bounds__(kBlock) k_rhs_irr(int nrows, const int64_t* __
   const int64_t c = cell[t];
   double v = src[t] * rho[c];
   for (int f = 0; f < 6; ++f) v -= cface[6 * t + f] * fv.v[f];
-  if (obj[t] >= 0) v -= cobj[t] * objv[obj[t]];
+  if (obj[t] >= 0) v -= cobj[t] * objv.v[obj[t]];
   if (sigma) v -= csig[t] * sigma[c];
   b[dof[t]] = v;
 }
@@ -2022,7 +2018,7 @@ __global__ void __launch_bounds__(kBlock) k_efield_irr(int ncell, int dim, int64
   double v = 0;
   for (int64_t z = rp[e]; z < rp[e + 1]; ++z) v += val[z] * (col[z] < N ? x[col[z]] : x2[col[z] - N]);
   for (int f = 0; f < 6; ++f) v += cface[6 * e + f] * fv.v[f];
-  if (obj[e] >= 0) v += cobj[e] * objv[obj[e]];
+  if (obj[e] >= 0) v += cobj[e] * objv.v[obj[e]];
   if (sigma) v += csig[e] * sigma[c];
   E[d * N + c] = v;
 }

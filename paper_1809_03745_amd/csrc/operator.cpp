@@ -654,9 +654,9 @@ void host_rhs(const Problem& pb, const double* rho, const double* sigma, const d
   const Level& L = pb.levels[0];
   const Grid& g = L.g;
   const FineData& F = pb.fine;
-  double bv[6], ov[64];
+  double bv[6], ov[kMaxObj];
   for (int f = 0; f < 6; ++f) bv[f] = bcv ? bcv[f] : pb.bc.value[f];
-  for (size_t k = 0; k < pb.geo.obj_value.size() && k < 64; ++k) ov[k] = objv ? objv[k] : pb.geo.obj_value[k];
+  for (size_t k = 0; k < pb.geo.obj_value.size(); ++k) ov[k] = objv ? objv[k] : pb.geo.obj_value[k];
   const int nk = g.dim == 3 ? g.n[2] : 1;
   for (int64_t q = 0; q < L.N + L.N2; ++q) b[q] = 0.0;
   for (int k = 0; k < nk; ++k)

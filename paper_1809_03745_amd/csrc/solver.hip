@@ -1496,13 +1496,14 @@ static void upload(ebmg_problem_s* P, bool batch_box = false, const ebmg_problem
   D.eobj.upload(eobj.data(), NE, s, by);
   D.ecobj.upload(ecobj.data(), NE, s, by);
   D.ecsig.upload(ecsig.data(), NE, s, by);
-  D.objv.alloc(std::max<int64_t>(1, (int64_t)H.geo.obj_value.size()), by);
   D.part.alloc(std::max<int64_t>(2 * kNormBlocks, 2 * matvec_blocks(D.lv[0])), by);
   D.scal.alloc(SC_NUM, by);
   HIPCHECK(hipHostMalloc((void**)&D.host_scal, (SC_NUM + 1) * sizeof(double), hipHostMallocCoherent));
   D.krylov = H.opt.krylov == 2;
   if (batch_box) {
-    // the in-group solver keeps its Krylov / correction vectors here
+    // the in-group solver reads the objects' values from memory and keeps its
+    // Krylov / correction vectors here
+    D.objv.alloc(std::max<int64_t>(1, (int64_t)H.geo.obj_value.size()), by);
     for (auto& k : D.kv) k.alloc(L0.N + L0.N2, by);
     HIPCHECK(hipStreamSynchronize(s));
     return;
@@ -2142,13 +2143,7 @@ static ObjVals object_values(ebmg_problem_s* P, const double* objv) {
   const double* v = objv ? objv : setup.data();
   ObjVals o;
   std::memset(&o, 0, sizeof(o));
-  if (setup.size() <= (size_t)kMaxObj) {
-    std::copy(v, v + setup.size(), o.v);
-  } else {
-    o.p = P->dev.objv.p;
-    HIPCHECK(hipMemcpyAsync(P->dev.objv.p, v, sizeof(double) * setup.size(), hipMemcpyHostToDevice, P->ctx->stream));
-    HIPCHECK(hipStreamSynchronize(P->ctx->stream));   // v may not outlive the copy
-  }
+  std::copy(v, v + setup.size(), o.v);   // (the set-up takes kMaxObj at most)
   return o;
 }
 
@@ -3514,7 +3509,7 @@ static void build_host_problem(ebmg::Problem& H, const ebmg_box* box, int nobj, 
 
 ebmg_status ebmg_setup(ebmg_ctx ctx, const ebmg_box* box, int32_t nobj, const ebmg_object* objs,
                        const ebmg_domain_bc* bc, const ebmg_options* opt, ebmg_problem* out) {
-  if (!ctx || !box || !bc || !out || (nobj > 0 && !objs) || nobj < 0 || nobj > 64) {
+  if (!ctx || !box || !bc || !out || (nobj > 0 && !objs) || nobj < 0 || nobj > kMaxObj) {
     if (ctx) ctx->err = "invalid argument to ebmg_setup";
     return EBMG_ERR_ARG;
   }
@@ -4130,7 +4125,7 @@ ebmg_status ebmg_setup_batch(ebmg_ctx ctx, int32_t nbox, const ebmg_box* boxes, 
     int prec = -1;
     for (int i = 0; i < nbox; ++i) {
       if (boxes[i].dim != Bt->dim) throw ArgError("all boxes of a batch must have the same dimension");
-      if (nobj[i] < 0 || nobj[i] > 64 || (nobj[i] > 0 && !objs[i])) throw ArgError("bad object list");
+      if (nobj[i] < 0 || nobj[i] > kMaxObj || (nobj[i] > 0 && !objs[i])) throw ArgError("bad object list");
       auto P = std::make_unique<ebmg_problem_s>();
       P->ctx = ctx;
       P->host = std::make_unique<Problem>();
@@ -4494,7 +4489,7 @@ static void family_free(ebmg_family_s* F) {
 
 ebmg_status ebmg_setup_family(ebmg_ctx ctx, const ebmg_box* box, int32_t nobj, const ebmg_object* objs,
                               int32_t nmem, const ebmg_domain_bc* bcs, const ebmg_options* opts, ebmg_family* out) {
-  if (!ctx || !box || !bcs || !opts || !out || (nobj > 0 && !objs) || nobj < 0 || nobj > 64 || nmem < 1 ||
+  if (!ctx || !box || !bcs || !opts || !out || (nobj > 0 && !objs) || nobj < 0 || nobj > kMaxObj || nmem < 1 ||
       nmem > 64) {
     if (ctx) ctx->err = "invalid argument to ebmg_setup_family";
     return EBMG_ERR_ARG;
@@ -4834,7 +4829,7 @@ ebmg_status ebmg_setup_amr(ebmg_ctx ctx, int32_t nbox, const ebmg_box* boxes, co
       const int lev = levels[l];
       if (B.dim != D) throw ArgError("every box has the base box's dimension");
       if (lev < 0 || lev > 12 || (l > 0 && lev == 0)) throw ArgError("bad level of an AMR box");
-      if (nobj[l] < 0 || nobj[l] > 64 || (nobj[l] > 0 && !objs[l])) throw ArgError("bad objects of a box");
+      if (nobj[l] < 0 || nobj[l] > kMaxObj || (nobj[l] > 0 && !objs[l])) throw ArgError("bad objects of a box");
       const double h = boxes[0].h / (double)(1 << lev);
       if (std::fabs(B.h - h) > 1e-12 * h) throw ArgError("a box of level l needs cells of size h0 / 2^l");
       ebmg::AmrBox& X = A->box[l];
