@@ -680,10 +680,9 @@ static void vcycle(DevProblem& D, const Options& o, size_t l, hipStream_t s, T* 
                    bool add = false);
 template <typename T>
 static bool from_zero(DevProblem& D, const Options& o);
+template <typename F>
+static void graph_run(hipGraphExec_t& exec, hipStream_t s, F&& body);
 
-// Tail autotuner: time a whole V-cycle (on zero vectors) with the one-
-// workgroup engine starting at each level of at most kTailMax unknowns, and
-// with no tail at all; keep the fastest.
 // Sweep timings alone rank the z-marching configurations of the finest level
 // only to within a few per cent; where the finest level uses one, the
 // fastest few are timed again inside whole V-cycles (the solve's own cache
@@ -730,6 +729,14 @@ static void refine_finest_zm(DevProblem& D, const Options& o, hipStream_t s) {
   D.tail_l0 = tail0;
 }
 
+// Tail autotuner: time a whole V-cycle (on zero vectors) with the one-
+// workgroup engine starting at each level of at most kTailMax unknowns, and
+// with no tail at all; keep the fastest. The cycles are run as a solve runs
+// them: a tiled level 0 only from x = 0 (by its phases, a 64^2 cycle by launches
+// was charged ten launches too many), and replayed from a graph where solves
+// replay theirs (timed launch by launch, a 64^3 Eddington box in mixed precision
+// took the engine for its 8^3 level in two set-ups of three, 1.6 ms a solve
+// against 0.90).
 template <typename T>
 static void tune_tail(DevProblem& D, const Options& o, hipStream_t s) {
   const int nl = (int)D.lv.size();
@@ -757,17 +764,26 @@ static void tune_tail(DevProblem& D, const Options& o, hipStream_t s) {
   D.tail_ms.assign(cand.size(), 0.0);
   for (size_t k = 0; k < cand.size(); ++k) {
     D.tail_l0 = cand[k];
-    // as a solve runs it: a tiled level 0 only from x = 0 (timed by its
-    // phases, a 64^2 cycle by launches was charged ten launches too many)
     const bool xz = from_zero<T>(D, o);
-    for (int r = 0; r < 2; ++r) vcycle<T>(D, o, 0, s, x, b, xz);
     const int reps = 5;
+    hipGraphExec_t exec = nullptr;
+    auto cycles = [&]() {
+      auto body = [&](hipStream_t q) {
+        for (int r = 0; r < reps; ++r) vcycle<T>(D, o, 0, q, x, b, xz);
+      };
+      if (o.graphs == 0)
+        graph_run(exec, s, body);
+      else
+        body(s);
+    };
+    cycles();
     HIPCHECK(hipEventRecord(e0, s));
-    for (int r = 0; r < reps; ++r) vcycle<T>(D, o, 0, s, x, b, xz);
+    cycles();
     HIPCHECK(hipEventRecord(e1, s));
     HIPCHECK(hipEventSynchronize(e1));
     float ms = 0;
     HIPCHECK(hipEventElapsedTime(&ms, e0, e1));
+    if (exec) HIPCHECK(hipGraphExecDestroy(exec));
     D.tail_ms[k] = ms / reps;
     if (ms / reps < best) {
       best = ms / reps;

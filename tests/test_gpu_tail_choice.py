@@ -26,7 +26,7 @@ def _kernels(fn):
     with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
         fn()
         torch.cuda.synchronize()
-    return sorted({e.name for e in prof.events() if "ebmg" in e.name})
+    return sorted({e.name for e in prof.events() if "ebmg" in e.name or "GraphLaunch" in e.name})
 
 
 @pytest.mark.parametrize("prec", [0, 1])
@@ -47,3 +47,16 @@ def test_tuner_times_the_solve_s_cycles(ctx, make, prec):
     assert any("k_tile" in n or "k_tail_vcycle" in n for n in names), names
     assert not [n for n in names if "k_rb" in n], names
     P.release()
+
+
+@pytest.mark.parametrize("graphs", [0, 1])
+def test_tuner_replays_graphs_where_solves_do(ctx, graphs):
+    pr, held = W.eddington(3, 32, 5.0, seed=1), []
+    setup = _kernels(lambda: held.append(ebmg.Problem(ctx, pr, precision=1, smoother=4, graphs=graphs)))
+    P = held[0]
+    rho = torch.ones(P.N, dtype=torch.float64, device=DEV)
+    phi = torch.zeros_like(rho)
+    solve = _kernels(lambda: P.solve(rho, phi))
+    P.release()
+    replays = [any("GraphLaunch" in n for n in names) for names in (setup, solve)]
+    assert replays == [graphs == 0, graphs == 0], (setup, solve)
