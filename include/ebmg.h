@@ -182,8 +182,8 @@ ebmg_status ebmg_destroy(ebmg_ctx ctx);
 const char* ebmg_last_error(ebmg_ctx ctx);
 
 /* Build geometry moments, the finest-level operator (cut-cell rows), the
- * multigrid hierarchy and the bottom-level inverse on the host, and upload
- * them (device contexts). Boundary-condition TYPES and object kinds are fixed
+ * multigrid hierarchy on the host and upload them (device contexts, which form
+ * the bottom-level inverse on the device). Boundary-condition TYPES and object kinds are fixed
  * here; values may change per solve.
  * Paper: Spatial discretization (cut cells from a level set: volume
  * fractions, apertures, centroids, linearised facets); Helmholtz equations
@@ -219,6 +219,10 @@ ebmg_status ebmg_query_level(ebmg_problem pb, int32_t level, int64_t* n_cells, i
  * chosen (or best
  * fused) variant's sweep time (ms) as the setup autotuner measured them (0 if
  * not timed).
+ * On a level whose V-cycle sides run as one launch each (3D up to 2^18 cells,
+ * 2D up to 2^20, with at most two sweeps, smoother 0 or 4 and explicit rows of
+ * short reach) solves make none of these sweeps; the choice is what ebmg_smooth
+ * and the timing hooks use there.
  * level = -1 reports the coarse-tail choice instead: *fused receives the first
  * level run by the one-workgroup engine (-1: none), *split_ms the V-cycle time
  * without it and *fused_ms the V-cycle time with the chosen tail. */
@@ -441,7 +445,9 @@ ebmg_status ebmg_time_kernel(ebmg_problem pb, int32_t which, int32_t level, int3
  * launch carries a HIP event pair that its dispatch stamps with the
  * kernel's own start and end (extended launch); while any timing is on,
  * those solves launch their kernels directly instead of replaying graphs (the same
- * kernels in the same order). enable = 0 stops it and reports the number of
+ * kernels in the same order; but a level timed with which = 0 whose V-cycle
+ * sides run as one launch each runs its sweeps, residual and transfers
+ * instead, whose iterates agree to rounding). enable = 0 stops it and reports the number of
  * launches timed, their mean duration (ms) and the algorithmic bytes of one
  * launch (as ebmg_time_kernel counts them). Outputs are HOST pointers and may
  * be NULL. ERR_ARG if enable = 0 finds no such timing running on that level. */
@@ -687,7 +693,9 @@ ebmg_status ebmg_mesh_query(ebmg_mesh m, int32_t* ntri, int32_t* nnode, int32_t*
  * a 3D box, written to sdf (DEVICE, prod(n[d]+1) doubles, x fastest: the
  * node-sampled level set ebmg_setup takes for an object, up to the sign
  * convention of the object kind). visits (HOST, nullable) receives the
- * number of tree boxes and triangles the search examined. Work is queued on
+ * number of tree boxes and triangles that came close enough to a node to be
+ * examined for it, summed over the nodes (the search examines them for groups
+ * of neighbouring nodes together). Work is queued on
  * the context's stream and waited for. */
 ebmg_status ebmg_mesh_sdf(ebmg_mesh m, const ebmg_box* box, double* sdf, int64_t* visits);
 

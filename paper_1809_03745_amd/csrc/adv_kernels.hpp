@@ -250,8 +250,8 @@ __device__ __forceinline__ T& at(T* p, unsigned o) {
 // 57 % of the launch's cycles at four wavefronts a SIMD) and the loads'
 // latency. A form with 16 x 16-cell tiles, whose threads each computed both
 // faces of two axes in branches and one wavefront of four the halo, took
-// 333 us for 256^3 cells (2.1 TB/s of the 41 B per cell); this one 195 us
-// (3.5 TB/s). Unrolled over the roles of the carried planes, without their
+// 333 us for 256^3 cells (2.1 TB/s of the 41 B per cell); this one 195 to 204
+// us (3.4 to 3.5 TB/s). Unrolled over the roles of the carried planes, without their
 // moves, it spilled 75 registers and took 465 us.
 template <int R, int ZC>
 __global__ void __launch_bounds__(64 * R) k_adv_rows(const double* __restrict__ n, const uint8_t* __restrict__ cls,

@@ -3,9 +3,10 @@
 // polygon, edge or vertex, found through a bounding-volume hierarchy by a
 // nearest-first closest-feature search): the search keeps the best squared
 // distance found so far and descends into the nearer child box first, pushing
-// the farther one while its box could still hold a closer triangle. The sign is that of (p - c) . n, with c the closest point
-// and n the angle-weighted pseudonormal of the feature c lies on (face, edge
-// or vertex), prepared on the host (mesh.cpp). FP64 throughout.
+// the farther one while its box could still hold a closer triangle. The sign is
+// that of (p - c) . n, with c the closest point and n the angle-weighted
+// pseudonormal of the feature c lies on (face, edge or vertex), prepared on the
+// host (mesh.cpp). FP64 throughout.
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -976,9 +976,11 @@ static void upload_bottom_krylov(DevProblem& D, hipStream_t s) {
 }
 
 // Whether no row's off-diagonal entries outweigh its diagonal, and some row's
-// fall clearly short of it (plain boxes with a mass or a value on some face;
-// elimination in the given order is then as safe as with pivoting, and the
-// singular pure-flux box keeps the search and its refusal).
+// fall clearly short of it (plain boxes with a mass or a value on some face):
+// elimination in the given order is then as safe as with pivoting. A pure-flux
+// box, which only new coefficients can make (set-ups refuse it), keeps the
+// search; neither form refuses it, since rounding leaves its last pivot at some
+// 1e-12 instead of 0, as the elimination on the host does.
 static bool row_dominant(const Level& L) {
   std::vector<std::pair<int64_t, double>> row;
   bool strict = false;
@@ -1203,10 +1205,13 @@ static bool recoefficientable(const Problem& H) {
 // Levels of at most this many cells take the one-launch V-cycle sides.
 // Measured per V-cycle side against the launches it replaces (FP64, two
 // sweeps): 2D 1024^2 with rows of reach 3 26 us against 60, 512^2 (reach 2)
-// 14 against 45, 256^2 and below 9 to 11 against 21; 3D 64^3 18 against 27,
-// 32^3 and 16^3 9 to 10 against 21 (12 to 18 with many rows). At 128^3 the
-// eightfold cell work would cost about 130 us against 60; 2D levels above
-// 1024^2 were not measured and keep their sweeps.
+// 14 against 45, 256^2 and below 9 to 11 against 21; 3D without rows 64^3 18
+// against 27, 32^3 and 16^3 9 to 10 against 21. With the rows of a 256^3 pin
+// (FP32, the side down and the side up): 64^3 28 and 27 against 40 and 27,
+// 32^3 18 and 15 against 27 and 23, 16^3 15 and 12. The ends are not crossings:
+// 2D levels above 1024^2 were not measured and keep their sweeps, and that the
+// eightfold cell work costs more at 128^3 (about 130 us against 60) is an
+// estimate from 64^3.
 constexpr int64_t kTileMax2 = 1 << 20, kTileMax3 = 1 << 18;
 
 // The tiles of level L (rows in device order, C the next coarser level), or

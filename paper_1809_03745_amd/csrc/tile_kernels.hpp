@@ -18,7 +18,8 @@
 //
 // A launch waits on latency: about 4 us to start, three dependent loads (the
 // tile's list, its rows, their values), then 0.6 us a phase; 8 to 11 us at
-// 16^3, 32^3 and 32^2 to 256^2. Row entries held in registers over the phases
+// 16^3, 32^3 and 32^2 to 256^2 (12 to 18 us at 16^3 and 32^3 with the rows of a
+// pin, 28 us at 64^3). Row entries held in registers over the phases
 // did not change it (they come from L2 while the template cells compute).
 // Two 1024-thread workgroups fit a CU where the launch bounds say so, 33 -> 26
 // us at 1024^2. Bounds are set so that nothing spills.

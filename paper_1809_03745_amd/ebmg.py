@@ -735,7 +735,7 @@ class Mesh:
     def sdf(self, n, h, lo, out):
         """Signed distance at the nodes of an n[0] x n[1] x n[2]-cell box
         (out: device float64 tensor of prod(n+1) entries); returns the number
-        of boxes and triangles the search examined."""
+        of boxes and triangles examined for a node, summed over the nodes."""
         box = Box()
         box.dim = 3
         for d in range(3):
