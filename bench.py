@@ -238,6 +238,16 @@ def _kname(raw):
     return n.replace(" ", "")
 
 
+def _finest(rows, counter):
+    """The dispatches of one kernel and grid that ran on the finest level:
+    levels may share a grid (blocks of small levels walk fewer planes), and the
+    next one has an eighth of the cells, so those with at least half the
+    largest value of a counter that grows with them."""
+    size = {r["Dispatch_Id"]: float(r["Counter_Value"]) for r in rows if r["Counter_Name"] == counter}
+    top = max(size.values(), default=0.0)
+    return {i for i, v in size.items() if v >= 0.5 * top}
+
+
 def pmc_summary(fetch_csv, write_csv, command):
     """Reduce the two counter passes of ``--pmc-probe`` to HBM bytes per
     launch of each finest-level kernel and write the committed summary."""
@@ -248,8 +258,12 @@ def pmc_summary(fetch_csv, write_csv, command):
         d = collections.defaultdict(list)
         with open(path) as fh:
             for r in csv.DictReader(fh):
-                d[(_kname(r["Kernel_Name"]), int(r["Grid_Size"]))].append(float(r["Counter_Value"]))
-        return d
+                d[(_kname(r["Kernel_Name"]), int(r["Grid_Size"]))].append(r)
+        out = {}
+        for k, rows in d.items():
+            keep = _finest(rows, rows[0]["Counter_Name"])
+            out[k] = [float(r["Counter_Value"]) for r in rows if r["Dispatch_Id"] in keep]
+        return out
 
     f, w = load(fetch_csv), load(write_csv)
 
@@ -397,11 +411,18 @@ def pmc_inst_summary(csvs, command):
     d = collections.defaultdict(lambda: collections.defaultdict(list))
     meta = {}
     for path in csvs:
+        by = collections.defaultdict(list)
         with open(path) as fh:
             for r in csv.DictReader(fh):
                 k = (_kname(r["Kernel_Name"]), int(r["Grid_Size"]))
-                d[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
+                by[k].append(r)
                 meta[k] = (r["Workgroup_Size"], r["LDS_Block_Size"], r["VGPR_Count"], r["SGPR_Count"])
+        for k, rows in by.items():
+            names = {r["Counter_Name"] for r in rows}
+            keep = _finest(rows, "SQ_INSTS_VALU" if "SQ_INSTS_VALU" in names else "SQ_ACTIVE_INST_VALU")
+            for r in rows:
+                if r["Dispatch_Id"] in keep:
+                    d[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
     names = sorted({k[0] for k in d if k[0].startswith(("k_rb_zm3", "k_rb_zq3", "k_rb<", "k_rb_tile3", "k_resid_zp3"))})
     lines = [f"# Instruction counters of the finest-level sweep kernels, 256^3 pin-plane (rocprofv3 --pmc)\n",
              "Commands (from the repository root on the GPU host; one counter pass per run):\n",
