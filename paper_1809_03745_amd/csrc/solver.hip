@@ -5203,10 +5203,6 @@ ebmg_status ebmg_mesh_sdf(ebmg_mesh m, const ebmg_box* box, double* sdf, int64_t
     hipStream_t s = ctx->stream;
     unsigned long long* vis = visits ? m->visits.p : nullptr;
     if (vis) HIPCHECK(hipMemsetAsync(vis, 0, sizeof(unsigned long long), s));
-    // 4 x 4 x 4 nodes a wavefront share the most; with fewer than some two
-    // wavefronts a SIMD the walk of the slowest one is the time, and smaller
-    // bricks shorten it (pin, 33^3 nodes: 0.63 against 0.41 ms; 65^3: 0.52
-    // against 0.55)
     auto launch = [&](auto kernel, int bx, int by, int bz) {
       const int64_t nw = (int64_t)((m0 + bx - 1) / bx) * ((m1 + by - 1) / by) * ((m2 + bz - 1) / bz);
       const int64_t nb = (nw + kSdfBlock / 64 - 1) / (kSdfBlock / 64);
@@ -5214,10 +5210,41 @@ ebmg_status ebmg_mesh_sdf(ebmg_mesh m, const ebmg_box* box, double* sdf, int64_t
                          (const DevDisc*)m->disc.p, (const DevSearchTri*)m->search.p, m->tri.p, m0, m1, m2, box->h,
                          box->lo[0], box->lo[1], box->lo[2], sdf, vis);
     };
-    if ((int64_t)m0 * m1 * m2 >= 64 * 2048)
+    // 4 x 4 x 4 nodes a wavefront share the most. On small lattices the walk of
+    // the slowest wavefront is the time (nodes at like distance from many
+    // triangles: the axis of a pin), and a brick of fewer nodes walks less; the
+    // more so, the finer the mesh is against the lattice (fine: triangles a node
+    // of a lattice plane). On a mesh of few triangles no walk is long. ms with
+    // (1, 1, 1), (2, 2, 1), (4, 2, 1), (4, 2, 2), (4, 4, 4):
+    //   pin of 6144 triangles, 9^3 nodes   0.20  0.22   -    0.70  1.53
+    //                          25^3        0.36  0.25  0.27  0.53  0.75
+    //                          49^3        1.53  0.59  0.41  0.39  0.77
+    //                          57^3         -    0.83  0.53  0.57  0.67
+    //                          65^3        3.33  1.11  0.65  0.54  0.52
+    //   pin of 24576, 49^3                 2.23  1.01  0.92  1.01  2.21
+    //                 57^3                 3.23  1.32  1.10  1.56  1.97
+    //                 65^3                 4.59  1.71  1.23  1.16  1.51
+    //                 97^3                13.8   4.45  2.61  1.82  1.75
+    //   cube of 12, 49^3                   0.45  0.13   -    0.06  0.04
+    // One search a thread was still the faster one at 49^3 and 57^3 nodes along
+    // the finer pin when it stands along z or y (0.89 and 1.01, 0.95 and 1.24 ms
+    // against 0.93 and 1.06, 1.11 and 1.36), not along x (2.08 and 2.16 against
+    // 1.97 and 1.92) or askew (2.34 and 2.64 against 0.99 and 1.28).
+    const int64_t nodes = (int64_t)m0 * m1 * m2;
+    const double fine = (double)m->ntri / std::cbrt((double)nodes * nodes);
+    const bool mid = nodes <= ((int64_t)1 << 19);
+    if (m->ntri < 512)
       launch(k_sdf_mesh<4, 4, 4>, 4, 4, 4);
-    else
+    else if (nodes <= 1024)   // one a SIMD
+      launch(k_sdf_mesh<1, 1, 1>, 1, 1, 1);
+    else if (nodes <= ((int64_t)1 << 16))
+      launch(k_sdf_mesh<2, 2, 1>, 2, 2, 1);
+    else if (mid && fine >= 7.0)
+      launch(k_sdf_mesh<4, 2, 1>, 4, 2, 1);
+    else if (nodes <= ((int64_t)3 << 16) || (mid && fine >= 4.0))
       launch(k_sdf_mesh<4, 2, 2>, 4, 2, 2);
+    else
+      launch(k_sdf_mesh<4, 4, 4>, 4, 4, 4);
     HIPCHECK(hipGetLastError());
     if (visits) {
       unsigned long long v = 0;
